@@ -300,6 +300,13 @@ const char* fdd_plan_kernel(fdd_plan_t plan);
  * All three are 0 for a plan that is not factorised.  Any output pointer may be NULL. */
 fdd_status fdd_plan_factors(fdd_plan_t plan, int32_t* fine, int32_t* coarse, int32_t* col_tiles);
 
+/* Infrastructure: the grid form of the phasor sum.  Where the trials are runs of equal DM steps and
+ * the delays are exact, fdd_execute and fdd_power_spectrum evaluate Eq. 7 per bin as a non-uniform
+ * Fourier transform along the trial axis, in float32 at every precision setting; fdd_plan_kernel and
+ * fdd_plan_factors then name the family that the plan falls back to.  n_runs: number of runs (0: the
+ * named family does the sums); points: grid points of the largest.  Either pointer may be NULL. */
+fdd_status fdd_plan_grid(fdd_plan_t plan, int32_t* n_runs, int32_t* points);
+
 /* Infrastructure: text of a status code, and of the calling thread's most recent failure. */
 const char* fdd_status_string(fdd_status s);
 const char* fdd_last_error(void);

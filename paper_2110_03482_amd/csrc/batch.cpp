@@ -40,7 +40,7 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-enum Kind { kValu = 0, kMfmaF32 = 1, kSplitF16 = 2, kSplitBf16 = 3, kFac = 4 };
+enum Kind { kValu = 0, kMfmaF32 = 1, kSplitF16 = 2, kSplitBf16 = 3, kFac = 4, kGrid = 5 };
 
 struct Choice {
   int kind = kValu;
@@ -55,6 +55,7 @@ struct Choice {
       case kSplitBf16: std::snprintf(buf, sizeof buf, "mfma_bf16_split/%s", persist ? "persistent" : "grid"); break;
       case kFac: std::snprintf(buf, sizeof buf, "fac_%s/%s", variant == FDD_FP32 ? "f32" : variant == FDD_FP16_SPLIT ? "f16_split" : "bf16_split",
                                persist ? "persistent" : "grid"); break;
+      case kGrid: std::snprintf(buf, sizeof buf, "grid"); break;
       default: std::snprintf(buf, sizeof buf, "valu/nk%d", variant); break;
     }
     return buf;
@@ -79,6 +80,8 @@ struct Stack {
   size_t ftab = 0;                   // DM-factorised tables (table arena), if fine > 0
   int fine = 0, coarse = 0;          // DM factorisation (0: DM list not uniform, or rounded delays)
   double dm0 = 0.0, step = 0.0;
+  std::vector<GridRun> grid;         // grid form of the phasor sum (offsets in the table arena), or empty
+  size_t perm = 0;                   // its channel order (table arena)
   size_t tw = 0;                     // twiddles (table arena)
   size_t l1 = 0;                     // per-chunk L1 maxima (word index in the small arena), split only
   size_t X = 0, Yr = 0, Yi = 0;      // offsets in the stack's scratch
@@ -101,6 +104,7 @@ struct Launch {
   Stage stage = kR2c;
   int wave = 0;
   int log_n = 0;              // FFT stages: log2(L / 2)
+  bool inter = false;         // inverse FFT: Y as interleaved complex (the grid form writes it)
   bool u8 = false;
   int cls = -1;               // phasor stage
   std::vector<int> beams;     // beams (transpose, FFT stages) or stacks (phasor stage)
@@ -161,6 +165,7 @@ struct fdd_batch_s {
   int n_waves = 0;
   uint32_t flags = 0;
   std::string cache_path, arch;
+  size_t sched = 0;                  // schedule scratch of the grid form (table arena)
   uint8_t* d_tab = nullptr;
   size_t tab_bytes = 0;
   uint8_t* d_scr = nullptr;
@@ -241,6 +246,46 @@ Class make_class(const fdd_plan_s* p, int N, bool fac, bool fac_default) {
   return c;
 }
 
+// The class of the stacks whose phasor sums take the grid form: one kernel, nothing to tune.
+Class grid_class(const fdd_plan_s* p) {
+  Class c;
+  char key[64];
+  std::snprintf(key, sizeof key, "grid/L%lld", (long long)p->L);
+  c.key = key;
+  c.cands.push_back({kGrid, 0, false});
+  c.ms.assign(1, -1.0f);
+  c.settled = true;
+  return c;
+}
+
+hipError_t launch_grid_stack(const fdd_batch_s* b, const Stack& sk, hipStream_t st) {
+  const fdd_plan_s* p = sk.rep;
+  uint8_t* scr = b->d_scr + sk.scratch;
+  for (const GridRun& r : sk.grid) {
+    GridArgs a;
+    a.X = (const float2*)(scr + sk.X);
+    a.ctab = (const uint4*)(b->d_tab + r.ctab);
+    a.dec = (const float*)(b->d_tab + r.dec);
+    a.perm = (const int*)(b->d_tab + sk.perm);
+    a.sched = (uint4*)(b->d_tab + b->sched);
+    a.sched_len = grid_sched_len(p->desc.n_chan);
+    a.inc_min = r.inc_min;
+    a.inc_max = r.inc_max;
+    a.Yc = (float2*)(scr + sk.Yr) + (size_t)r.j0 * (size_t)sk.n_chunks * (size_t)p->pitch;
+    a.n_dm = r.n;
+    a.n_chan = p->desc.n_chan;
+    a.n_chunks = sk.n_chunks;
+    a.log_m = r.log_m;
+    a.blk = r.blk;
+    a.n_blk = r.n_blk;
+    a.n_bins = (int)p->n_bins;
+    a.pitch = p->pitch;
+    const hipError_t e = launch_phasor_grid(a, st);
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 // Scratch bytes of one stack: its members' transposed 8-bit inputs, X and the two Y planes.
 size_t stack_scratch(fdd_batch_s* b, Stack* sk) {
   const fdd_plan_s* p = sk->rep;
@@ -274,6 +319,10 @@ fdd_status fill(fdd_batch_s* b, const void* const* in, float* const* out) {
   std::fill(b->h_desc.begin(), b->h_desc.end(), 0);
   for (Launch& l : b->launches) {
     if (l.stage == kTranspose) continue;
+    if (l.stage == kPhasor && chosen(b, l).kind == kGrid) {
+      l.total = (int)l.beams.size();
+      continue;
+    }
     int64_t acc = 0;
     int* prefix = (int*)(b->h_desc.data() + l.prefix);
     int nd = 0;                                     // descriptors written
@@ -348,10 +397,11 @@ fdd_status fill(fdd_batch_s* b, const void* const* in, float* const* out) {
           else f.in_f32 = (const float*)in[l.beams[i]];
           f.X = (float2*)(scr + sk.X) + (size_t)bm.koff * (size_t)p->pitch;
           f.n_rows = d.n_chan;
-          f.l1max = d.precision != FDD_FP32 ? b->d_small + sk.l1 + bm.koff : nullptr;
+          f.l1max = d.precision != FDD_FP32 && sk.grid.empty() ? b->d_small + sk.l1 + bm.koff : nullptr;
         } else {
           f.Yr = (const float*)(scr + sk.Yr) + (size_t)bm.koff * (size_t)p->pitch;
           f.Yi = (const float*)(scr + sk.Yi) + (size_t)bm.koff * (size_t)p->pitch;
+          if (l.inter) f.Yc = (const float2*)(scr + sk.Yr) + (size_t)bm.koff * (size_t)p->pitch;
           f.out = out[l.beams[i]];
           f.keep = d.single_chunk ? d.n_samp : p->S;
           f.n_rows = d.n_dm;
@@ -392,9 +442,16 @@ hipError_t enqueue_launch(fdd_batch_s* b, const Launch& l, const void* const* in
       g.prefix = (const int*)(b->d_desc + l.prefix);
       g.n_beams = l.n_desc;
       g.total = l.total;
-      return l.stage == kR2c ? launch_r2c_grouped(l.log_n, l.u8, g, st) : launch_c2r_grouped(l.log_n, g, st);
+      return l.stage == kR2c ? launch_r2c_grouped(l.log_n, l.u8, g, st) : launch_c2r_grouped(l.log_n, l.inter, g, st);
     }
     case kPhasor: {
+      if (chosen(b, l).kind == kGrid) {
+        for (int i : l.beams) {
+          const hipError_t e = launch_grid_stack(b, b->stacks[(size_t)i], st);
+          if (e != hipSuccess) return e;
+        }
+        return hipSuccess;
+      }
       Group<PhasorArgs> g;
       g.beams = (const PhasorArgs*)(b->d_desc + l.args);
       g.prefix = (const int*)(b->d_desc + l.prefix);
@@ -583,7 +640,10 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
     // the kernel fdd_execute would pick: its own choice for a lone beam, the same rule for a stack
     const bool fac_default =
         sk.beams.size() == 1 ? p->fac_fine > 0 && p->facw_nt == 0 : (sk.fine > 0 && sk.n_chunks <= 2);
-    Class c = make_class(p, sk.n_chunks, sk.fine > 0, fac_default);
+    // the grid form where fdd_execute takes it (a stack by the same rule for its own chunk count)
+    if (!p->grid.empty()) (void)grid_runs(p, sk.n_chunks, &sk.grid);
+    if (!sk.grid.empty()) sk.fine = sk.coarse = 0;
+    Class c = sk.grid.empty() ? make_class(p, sk.n_chunks, sk.fine > 0, fac_default) : grid_class(p);
     auto it = class_of.find(c.key);
     if (it == class_of.end()) {
       std::string name;
@@ -613,7 +673,7 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
 
   // table arena: one twiddle table per FFT length, phase tables per stack
   std::map<int64_t, size_t> tw_of;
-  size_t off = 0;
+  size_t off = 0, sched_bytes = 0;   // the phasor launches of a batch follow each other: one schedule scratch
   for (Stack& sk : b->stacks) {
     const fdd_plan_s* p = sk.rep;
     auto it = tw_of.find(p->L);
@@ -622,6 +682,18 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
       off = align_up(off + (size_t)p->L * sizeof(float2));
     }
     sk.tw = it->second;
+    if (!sk.grid.empty()) {
+      sk.perm = off;
+      off = align_up(off + (size_t)p->desc.n_chan * sizeof(int));
+      for (GridRun& r : sk.grid) {
+        r.ctab = off;
+        off = align_up(off + (size_t)r.n_blk * (size_t)p->desc.n_chan * sizeof(uint4));
+        r.dec = off;
+        off = align_up(off + (sizeof(float) << (r.log_m - 1)));
+      }
+      sched_bytes = std::max(sched_bytes, (size_t)kGridBlocks * 4 * (size_t)grid_sched_len(p->desc.n_chan) * sizeof(uint4));
+      continue;
+    }
     sk.tab = off;
     off = align_up(off + (size_t)p->desc.n_chan * (size_t)p->desc.n_dm * sizeof(uint4));
     if (sk.fine > 0) {
@@ -629,6 +701,8 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
       off = align_up(off + (size_t)p->desc.n_chan * (size_t)(sk.coarse + sk.fine) * sizeof(uint4));
     }
   }
+  b->sched = off;
+  off = align_up(off + sched_bytes);
   b->tab_bytes = off;
 
   // memory waves: first-fit decreasing over the stacks' scratch sizes
@@ -698,6 +772,7 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
         const fdd_plan_s* p = stage == kPhasor ? b->stacks[(size_t)g.second[0]].rep : b->beams[(size_t)g.second[0]].plan;
         l.log_n = p->log_len - 1;
         l.u8 = p->desc.input == FDD_IN_U8_TIME_MAJOR;
+        l.inter = stage == kC2r && g.first.second != 0;
         if (stage == kPhasor) {
           l.cls = g.first.first;
           l.ctr = words;
@@ -711,7 +786,10 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
       return std::make_pair(p->log_len, p->desc.input == FDD_IN_U8_TIME_MAJOR ? 1 : 0);
     });
     grouped(kPhasor, ws, [&](int i) { return std::make_pair(b->stacks[(size_t)i].cls, 0); });
-    grouped(kC2r, wb, [&](int i) { return std::make_pair(b->beams[(size_t)i].plan->log_len, 0); });
+    grouped(kC2r, wb, [&](int i) {
+      const Beam& bm = b->beams[(size_t)i];
+      return std::make_pair(bm.plan->log_len, b->stacks[(size_t)bm.stack].grid.empty() ? 0 : 1);
+    });
   }
   for (Stack& sk : b->stacks)
     if (sk.rep->desc.precision != FDD_FP32) {
@@ -748,7 +826,7 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
   if (s == FDD_OK) s = alloc((void**)&b->d_small, b->small_words * sizeof(unsigned int), "batch counters");
   if (s == FDD_OK) s = alloc((void**)&b->d_desc, b->h_desc.size(), "batch descriptors");
   if (s == FDD_OK) {
-    std::vector<uint8_t> tabs(b->tab_bytes, 0);
+    std::vector<uint8_t> tabs(b->sched, 0);
     for (const auto& kv : tw_of) {
       std::vector<float2> tw;
       twiddle_table(kv.first, &tw);
@@ -756,6 +834,19 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
     }
     for (const Stack& sk : b->stacks) {
       std::vector<uint4> tab;
+      if (!sk.grid.empty()) {
+        std::vector<int> order;
+        grid_order(sk.rep, &order);
+        std::memcpy(tabs.data() + sk.perm, order.data(), order.size() * sizeof(int));
+        for (const GridRun& r : sk.grid) {
+          grid_table(sk.rep, r, &tab);
+          std::memcpy(tabs.data() + r.ctab, tab.data(), tab.size() * sizeof(uint4));
+          std::vector<float> dv;
+          grid_divisors(r.log_m, &dv);
+          std::memcpy(tabs.data() + r.dec, dv.data(), dv.size() * sizeof(float));
+        }
+        continue;
+      }
       phase_table(sk.rep, &tab);
       std::memcpy(tabs.data() + sk.tab, tab.data(), tab.size() * sizeof(uint4));
       if (sk.fine > 0) {
@@ -763,7 +854,7 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
         std::memcpy(tabs.data() + sk.ftab, tab.data(), tab.size() * sizeof(uint4));
       }
     }
-    hipError_t e = hipMemcpy(b->d_tab, tabs.data(), b->tab_bytes, hipMemcpyHostToDevice);
+    hipError_t e = hipMemcpy(b->d_tab, tabs.data(), tabs.size(), hipMemcpyHostToDevice);
     if (e != hipSuccess) s = hip_fail(e, "hipMemcpy(batch tables)");
   }
   if (s == FDD_OK && !(b->flags & FDD_BATCH_NO_GRAPH)) {

@@ -9,7 +9,6 @@
 using namespace fdd;
 
 // The static scratch of fdd_execute_noalloc (see scratch_address below for how host code reaches it).
-static constexpr size_t kNoallocScratchBytes = size_t(64) << 20;
 static __device__ __align__(256) uint8_t scratch[kNoallocScratchBytes];
 
 namespace {
@@ -30,7 +29,11 @@ void mark(fdd_plan_t p, int i, hipStream_t st) {
   if (i == 4) ++p->prof_calls;
 }
 
-fdd_status forward(fdd_plan_t p, const void* in, hipStream_t st) {
+// Whether the phasor sums of fdd_execute and fdd_power_spectrum run in the grid kernel, which reads
+// plain float32 spectra whatever the plan's precision (no chunk scales, no split words).
+bool uses_grid(fdd_plan_t p) { return !p->grid.empty(); }
+
+fdd_status forward(fdd_plan_t p, const void* in, bool scales, hipStream_t st) {
   const fdd_plan_desc& d = p->desc;
   FftArgs f;
   if (d.input == FDD_IN_U8_TIME_MAJOR) {
@@ -49,7 +52,7 @@ fdd_status forward(fdd_plan_t p, const void* in, hipStream_t st) {
   f.pitch = p->pitch;
   f.n_chunks = (int)p->n_chunks;
   f.n_rows = d.n_chan;
-  if (d.precision != FDD_FP32) f.l1max = (unsigned int*)(p->d_ws + p->ws.scale);
+  if (scales) f.l1max = (unsigned int*)(p->d_ws + p->ws.scale);
   f.log_n = p->log_len - 1;
   hipError_t e = f.log_n > kMaxBlockLogN
                      ? launch_r2c_long(f, (float2*)(p->d_ws + p->ws.Z), (float*)(p->d_ws + p->ws.l1), st)
@@ -100,6 +103,34 @@ PhasorArgs segment_args(fdd_plan_t p, const PhasorArgs& all, const Segment& sg, 
   return a;
 }
 
+// One run of equally spaced trials: the arguments of its segment with the run's rows and tables.
+hipError_t launch_grid_run(fdd_plan_t p, const GridRun& r, const PhasorArgs& all, bool power, hipStream_t st) {
+  const PhasorArgs s = segment_args(p, all, p->segs[(size_t)r.seg], power);
+  const size_t row = (size_t)(r.j0 - p->segs[(size_t)r.seg].j0);
+  GridArgs a;
+  a.X = s.X;
+  a.ctab = (const uint4*)(p->d_ws + r.ctab);
+  a.dec = (const float*)(p->d_ws + r.dec);
+  a.perm = (const int*)(p->d_ws + p->ws.grid);
+  a.sched = (uint4*)(p->d_ws + p->ws.sched);
+  a.sched_len = grid_sched_len(s.n_chan);
+  a.inc_min = r.inc_min;
+  a.inc_max = r.inc_max;
+  if (power) a.P = s.P + row * (size_t)s.n_pow_bins;
+  else a.Yc = s.Yc + row * (size_t)s.n_chunks * (size_t)s.pitch;
+  a.n_dm = r.n;
+  a.n_chan = s.n_chan;
+  a.n_chunks = s.n_chunks;
+  a.log_m = r.log_m;
+  a.blk = r.blk;
+  a.n_blk = r.n_blk;
+  a.n_bins = s.n_bins;
+  a.n_pow_bins = s.n_pow_bins;
+  a.pitch = s.pitch;
+  a.dc_add = s.dc_add;
+  return launch_phasor_grid(a, st);
+}
+
 // The direct matrix-core phasor sums (Eq. 7 batched over the overlap-save chunks), one launch
 // per chunk group.
 hipError_t launch_direct(fdd_plan_t p, const PhasorArgs& a, hipStream_t st) {
@@ -115,7 +146,7 @@ hipError_t launch_direct(fdd_plan_t p, const PhasorArgs& a, hipStream_t st) {
 
 // The direct split kernels read X as split words: convert it once for all segments.
 hipError_t presplit(fdd_plan_t p, hipStream_t st) {
-  if (p->fac_fine > 0 || (p->kernel != "mfma_f16_split" && p->kernel != "mfma_bf16_split")) return hipSuccess;
+  if (uses_grid(p) || p->fac_fine > 0 || (p->kernel != "mfma_f16_split" && p->kernel != "mfma_bf16_split")) return hipSuccess;
   return launch_split_x((float2*)(p->d_ws + p->ws.X), (const unsigned int*)(p->d_ws + p->ws.scale),
                         p->desc.n_chan, (int)p->n_chunks, p->pitch, p->kernel == "mfma_bf16_split", st);
 }
@@ -193,15 +224,20 @@ namespace {
 fdd_status execute_body(fdd_plan_t p, const void* in, float* out, hipStream_t st) {
   fdd_status s;
   mark(p, 0, st);
-  s = forward(p, in, st);
+  s = forward(p, in, p->desc.precision != FDD_FP32 && !uses_grid(p), st);
   if (s != FDD_OK) return s;
   PhasorArgs all = phasor_args(p);
   all.Yr = (float*)(p->d_ws + p->ws.Yr);
   all.Yi = (float*)(p->d_ws + p->ws.Yi);
-  if (p->facw_nt > 0) all.Yc = (float2*)(p->d_ws + p->ws.Yr);   // both planes' memory, interleaved
+  if (p->facw_nt > 0 || uses_grid(p)) all.Yc = (float2*)(p->d_ws + p->ws.Yr);   // both planes' memory, interleaved
   hipError_t e = presplit(p, st);
   if (e != hipSuccess) return hip_fail(e, "split launch");
+  for (const GridRun& r : p->grid) {
+    e = launch_grid_run(p, r, all, false, st);
+    if (e != hipSuccess) return hip_fail(e, "phasor-sum launch");
+  }
   for (const Segment& sg : p->segs) {
+    if (uses_grid(p)) break;
     const PhasorArgs a = segment_args(p, all, sg, false);
     if (p->facw_nt > 0) e = launch_phasor_facw(a, p->desc.precision, p->facw_nt, st);
     else if (p->fac_fine > 0) e = launch_phasor_fac(a, p->desc.precision, st);
@@ -285,7 +321,7 @@ fdd_status fdd_power_spectrum(fdd_plan_t p, const void* in, float* out, void* st
   if (!p->desc.single_chunk) return fail(FDD_E_UNSUPPORTED, "power spectra need a single-chunk plan");
   hipStream_t st = (hipStream_t)stream;
   mark(p, 0, st);
-  s = forward(p, in, st);
+  s = forward(p, in, p->desc.precision != FDD_FP32 && !uses_grid(p), st);
   if (s != FDD_OK) return s;
   PhasorArgs all = phasor_args(p);
   all.P = out;
@@ -295,7 +331,12 @@ fdd_status fdd_power_spectrum(fdd_plan_t p, const void* in, float* out, void* st
     all.dc_add = 128.0f * (float)p->L * (float)p->desc.n_chan;
   hipError_t e = presplit(p, st);
   if (e != hipSuccess) return hip_fail(e, "split launch");
+  for (const GridRun& r : p->grid) {
+    e = launch_grid_run(p, r, all, true, st);
+    if (e != hipSuccess) return hip_fail(e, "phasor-sum launch");
+  }
   for (const Segment& sg : p->segs) {
+    if (uses_grid(p)) break;
     const PhasorArgs a = segment_args(p, all, sg, true);
     if (p->fac_fine > 0) e = launch_phasor_fac(a, p->desc.precision, st);
     else if (p->kernel == "mfma_f16_split") e = launch_phasor_split(a, false, st);
@@ -314,7 +355,7 @@ fdd_status fdd_power_spectrum_scaled(fdd_plan_t p, const void* in, float* out, v
   if (!p->scaled) return fail(FDD_E_UNSUPPORTED, "the plan was not made with FDD_PLAN_SCALED_DM");
   hipStream_t st = (hipStream_t)stream;
   mark(p, 0, st);
-  s = forward(p, in, st);
+  s = forward(p, in, p->desc.precision != FDD_FP32, st);
   if (s != FDD_OK) return s;
   const int prec = p->desc.precision;
   const bool split = prec != FDD_FP32;

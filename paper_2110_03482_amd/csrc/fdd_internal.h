@@ -48,6 +48,7 @@ struct LongPassArgs {
   float* out_real = nullptr;             // last inverse pass: real output [row][n_samp]
   const float* yr = nullptr;             // inverse pre-split: Y planes
   const float* yi = nullptr;
+  const float2* yc = nullptr;            // ... or Y as interleaved complex
   float* l1sum = nullptr;                // per-series L1 norm accumulation, or null
   int log_n = 0, log_ns = 0;
   int n_series = 0, n_chunks = 1;
@@ -88,6 +89,31 @@ struct PhasorArgs {
   // then not read.
   const uint4* ltab = nullptr;
   int lin_j0 = 0;
+};
+
+// Phasor sum of equally spaced trials with exact delays as a non-uniform Fourier transform along
+// the trial axis: n_blk blocks of blk trials, each on a grid of 2^log_m >= 2 blk points.
+struct GridArgs {
+  const float2* X = nullptr;        // [n_chan][n_chunks][pitch]
+  const uint4* ctab = nullptr;      // [n_blk][n_chan] {turns per bin of one DM step (lo, hi), of the
+                                    // block's centre trial blk / 2 (lo, hi)}
+  const int* perm = nullptr;        // [n_chan] channel of each table entry (entries by ascending delay)
+  uint4* sched = nullptr;           // scratch, sched_len entries per wave of the launch
+  int sched_len = 0;
+  uint64_t inc_min = 0, inc_max = 0; // smallest and largest turns per bin of one DM step
+  const float* dec = nullptr;       // [2^(log_m - 1)] row divisors (reciprocals)
+  float2* Yc = nullptr;             // [n_dm][n_chunks][pitch] complex, or
+  float* P = nullptr;               // [n_dm][n_pow_bins] power spectra (one chunk)
+  int n_dm = 0;
+  int n_chan = 0;
+  int n_chunks = 0;
+  int log_m = 0;
+  int blk = 0;
+  int n_blk = 0;
+  int n_bins = 0;
+  int n_pow_bins = 0;
+  int64_t pitch = 0;
+  float dc_add = 0.0f;              // added to Re Y at bin 0 before power (8-bit zero point)
 };
 
 // Spin-frequency-scaled DMs (Eq. 8) for power spectra of one chunk.  Block b covers bins
@@ -291,6 +317,13 @@ constexpr int kFacwNtMin = 4;
 constexpr int kFacwNtMax = 7;
 FacwChoice facw_choose(int n_dm, int n_chunks);
 hipError_t launch_phasor_facw(const PhasorArgs& a, int precision, int nt, hipStream_t st);
+// The non-uniform transform along the trial axis, and its row divisors.
+constexpr int kGridLogMin = 8, kGridLogMax = 12;   // grid points per column, 2^8 .. 2^12
+constexpr int kGridBlocks = 256;                    // workgroups of a launch at most (one per CU)
+// Schedule entries per wave: every channel once, in equal parts per lane.
+inline int grid_sched_len(int n_chan) { return (n_chan + 63) / 64 * 64; }
+hipError_t launch_phasor_grid(const GridArgs& a, hipStream_t st);
+void grid_divisors(int log_m, std::vector<float>* out);
 // Spin-frequency-scaled DMs: the per-block matrix products and the resampling in DM.
 // precision FDD_FP32: plain X; split precisions: X split in place by launch_split_x, and the
 // per-chunk L1 maxima for the scale.
@@ -300,7 +333,8 @@ hipError_t launch_scaled_resample(const ResampleArgs& a, hipStream_t st);
 // Grouped launches of the batched form.  Tiles per beam (for the prefix sums) come from the
 // *_tiles functions, which also fill a.n_dmt / a.n_bb where the kernel needs them.
 hipError_t launch_r2c_grouped(int log_n, bool u8, const Group<FftArgs>& g, hipStream_t st);
-hipError_t launch_c2r_grouped(int log_n, const Group<FftArgs>& g, hipStream_t st);
+// inter: every beam's Y is interleaved complex (Yc), else the planes
+hipError_t launch_c2r_grouped(int log_n, bool inter, const Group<FftArgs>& g, hipStream_t st);
 int64_t fft_grouped_tiles(const FftArgs& a);
 int64_t phasor_mfma_f32_tiles(PhasorArgs* a, int variant);
 hipError_t launch_phasor_mfma_f32_grouped(int nt, int variant, bool persist, const Group<PhasorArgs>& g,
@@ -325,6 +359,16 @@ struct Segment {
   size_t tw = 0;                      // workspace byte offset of its twiddles exp(-2 pi i j d / L), j < L/d
 };
 
+// A run of equally spaced trials inside one segment, summed by the grid kernel.
+struct GridRun {
+  int seg = 0;                        // its segment
+  int j0 = 0, n = 0;                  // trials j0 .. j0 + n - 1 of the plan
+  double dm0 = 0.0, step = 0.0;       // DM of trial j0, and the step
+  int log_m = 0, blk = 0, n_blk = 0;
+  size_t ctab = 0, dec = 0;           // workspace byte offsets
+  uint64_t inc_min = 0, inc_max = 0;  // smallest and largest turns per bin of one step
+};
+
 struct WorkspaceLayout {
   size_t tw = 0, tw_bytes = 0;        // float2 twiddles: L entries, then L/d for every other factor d
   size_t ptab = 0, ptab_bytes = 0;    // uint4 phase increments and step phasors, [n_chan][n] per segment
@@ -338,6 +382,8 @@ struct WorkspaceLayout {
   size_t ctab = 0, ctab_bytes = 0;    // scaled DMs: uint4 [n_chan] phase increments
   size_t ltab = 0, ltab_bytes = 0;    // linear phase increments: uint4 [n_chan] (uniform grid, exact delays)
   size_t dmv = 0, dmv_bytes = 0;      // scaled DMs: double [n_dm] trial DMs
+  size_t grid = 0, grid_bytes = 0;    // grid form: channel order, per-run channel tables and row divisors
+  size_t sched = 0, sched_bytes = 0;  // grid form: schedule scratch (in the phase table's place)
   size_t Q = 0, Q_bytes = 0;          // scaled DMs: float [n_dm + 64][q_pitch]
   size_t total = 0;
 };
@@ -369,6 +415,8 @@ struct fdd_plan_s {
   // the small tables on the host, uploaded into the workspace: (workspace byte offset, bytes)
   std::vector<std::pair<size_t, std::vector<uint8_t>>> htabs;
   std::vector<fdd::Segment> segs;
+  bool grid_force = false;              // FDD_GRID=1
+  std::vector<fdd::GridRun> grid;       // empty: the phasor sums run in the kernel family `kernel`
   int64_t out_total = 0;
   // spin-frequency-scaled DMs (FDD_PLAN_SCALED_DM)
   bool scaled = false;
@@ -392,8 +440,16 @@ void phase_table_rows(const fdd_plan_s* p, int j0, int n, std::vector<uint4>* ou
 // plus fine [n_chan][fine] phase tables of trial a * fine + b.
 bool uniform_grid(const std::vector<double>& dms, double* dm0, double* step);
 void factor_tables(const fdd_plan_s* p, int fine, int coarse, double dm0, double step, std::vector<uint4>* out);
+// Channel table of a grid run, [n_blk][n_chan].
+void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out);
+// The plan's trials as grid runs for n_chunks chunks; false if they have no such form or the kernel
+// family of the plan is the faster one.
+bool grid_runs(const fdd_plan_s* p, int n_chunks, std::vector<GridRun>* out);
+// Channels by ascending delay.
+void grid_order(const fdd_plan_s* p, std::vector<int>* out);
 // Enqueue the copies of the plan's host tables into a workspace at dst (same layout) on st.
 hipError_t upload_tables_async(const fdd_plan_s* p, uint8_t* dst, hipStream_t st);
+constexpr size_t kNoallocScratchBytes = size_t(64) << 20;   // the static scratch of fdd_execute_noalloc
 void set_error(const std::string& msg);
 fdd_status fail(fdd_status s, const std::string& msg);
 fdd_status hip_fail(hipError_t e, const char* what);

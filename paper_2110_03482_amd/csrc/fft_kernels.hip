@@ -295,7 +295,7 @@ __global__ __launch_bounds__(1 << (LOGN - LOGE)) void k_c2r(FftArgs a) {
   c2r_body<LOGN, LOGE, INTER>(a, blockIdx.x, blockIdx.y);
 }
 
-template <int LOGN, int LOGE>
+template <int LOGN, int LOGE, bool INTER>
 __global__ __launch_bounds__(1 << (LOGN - LOGE)) void k_c2r_grouped(Group<FftArgs> g) {
   const int bid = blockIdx.y * gridDim.x + blockIdx.x;
   if (bid >= g.total) return;
@@ -303,7 +303,7 @@ __global__ __launch_bounds__(1 << (LOGN - LOGE)) void k_c2r_grouped(Group<FftArg
   const FftArgs a = g.beams[b];
   const int lid = bid - g.prefix[b];
   if (lid >= a.n_chunks * a.n_rows) return;
-  c2r_body<LOGN, LOGE, false>(a, lid % a.n_chunks, lid / a.n_chunks);
+  c2r_body<LOGN, LOGE, INTER>(a, lid % a.n_chunks, lid / a.n_chunks);
 }
 
 // ----------------------------------------------------------------------------- long transforms
@@ -428,11 +428,17 @@ __global__ __launch_bounds__(256) void k_c2r_split(LongPassArgs a) {
   const int64_t f = (int64_t)blockIdx.x * 256 + threadIdx.x;
   if (f >= N) return;
   const int series = blockIdx.y;
-  const float* yr = a.yr + (int64_t)series * a.in_pitch;
-  const float* yi = a.yi + (int64_t)series * a.in_pitch;
-  const int64_t fm = N - f;
-  const float2 yf = make_float2(yr[f], f == 0 ? 0.0f : yi[f]);
-  const float2 ym = make_float2(yr[fm], fm == N ? 0.0f : -yi[fm]);       // conj Y[N - f]
+  const int64_t fm = N - f, at = (int64_t)series * a.in_pitch;
+  float2 yf, ym;
+  if (a.yc != nullptr) {
+    yf = a.yc[at + f];
+    ym = a.yc[at + fm];
+  } else {
+    yf = make_float2(a.yr[at + f], a.yi[at + f]);
+    ym = make_float2(a.yr[at + fm], a.yi[at + fm]);
+  }
+  if (f == 0) yf.y = ym.y = 0.0f;
+  ym.y = -ym.y;                                                           // conj Y[N - f]
   const float2 av = make_float2(0.5f * (yf.x + ym.x), 0.5f * (yf.y + ym.y));
   const float2 d = make_float2(0.5f * (yf.x - ym.x), 0.5f * (yf.y - ym.y));
   const float2 w = turn_phasor<true>((uint32_t)f << (31 - a.log_n));         // exp(+2 pi i f / L)
@@ -551,6 +557,7 @@ hipError_t launch_c2r_long(const FftArgs& f, float2* work, float2* work2, hipStr
   a.out_real = f.out;
   a.yr = f.Yr;
   a.yi = f.Yi;
+  a.yc = f.Yc;
   a.in_pitch = f.pitch;
   a.out = work;
   a.out_pitch = (int64_t)1 << a.log_n;
@@ -619,9 +626,11 @@ hipError_t launch_r2c_grouped_n(bool u8, const Group<FftArgs>& g, hipStream_t st
 }
 
 template <int LOGN>
-hipError_t launch_c2r_grouped_n(const Group<FftArgs>& g, hipStream_t st) {
+hipError_t launch_c2r_grouped_n(bool inter, const Group<FftArgs>& g, hipStream_t st) {
   constexpr int LOGE = fft_loge_inv<LOGN>();
-  hipLaunchKernelGGL((k_c2r_grouped<LOGN, LOGE>), linear_grid(g.total), dim3(1 << (LOGN - LOGE)), 0, st, g);
+  const dim3 grid = linear_grid(g.total), block(1 << (LOGN - LOGE));
+  if (inter) hipLaunchKernelGGL((k_c2r_grouped<LOGN, LOGE, true>), grid, block, 0, st, g);
+  else hipLaunchKernelGGL((k_c2r_grouped<LOGN, LOGE, false>), grid, block, 0, st, g);
   return hipGetLastError();
 }
 
@@ -708,20 +717,20 @@ hipError_t launch_r2c_grouped(int log_n, bool u8, const Group<FftArgs>& g, hipSt
   }
 }
 
-hipError_t launch_c2r_grouped(int log_n, const Group<FftArgs>& g, hipStream_t st) {
+hipError_t launch_c2r_grouped(int log_n, bool inter, const Group<FftArgs>& g, hipStream_t st) {
   if (g.total <= 0) return hipSuccess;
   switch (log_n) {
-    case 5: return launch_c2r_grouped_n<5>(g, st);
-    case 6: return launch_c2r_grouped_n<6>(g, st);
-    case 7: return launch_c2r_grouped_n<7>(g, st);
-    case 8: return launch_c2r_grouped_n<8>(g, st);
-    case 9: return launch_c2r_grouped_n<9>(g, st);
-    case 10: return launch_c2r_grouped_n<10>(g, st);
-    case 11: return launch_c2r_grouped_n<11>(g, st);
-    case 12: return launch_c2r_grouped_n<12>(g, st);
-    case 13: return launch_c2r_grouped_n<13>(g, st);
-    case 14: return launch_c2r_grouped_n<14>(g, st);
-    case 15: return launch_c2r_grouped_n<15>(g, st);
+    case 5: return launch_c2r_grouped_n<5>(inter, g, st);
+    case 6: return launch_c2r_grouped_n<6>(inter, g, st);
+    case 7: return launch_c2r_grouped_n<7>(inter, g, st);
+    case 8: return launch_c2r_grouped_n<8>(inter, g, st);
+    case 9: return launch_c2r_grouped_n<9>(inter, g, st);
+    case 10: return launch_c2r_grouped_n<10>(inter, g, st);
+    case 11: return launch_c2r_grouped_n<11>(inter, g, st);
+    case 12: return launch_c2r_grouped_n<12>(inter, g, st);
+    case 13: return launch_c2r_grouped_n<13>(inter, g, st);
+    case 14: return launch_c2r_grouped_n<14>(inter, g, st);
+    case 15: return launch_c2r_grouped_n<15>(inter, g, st);
     default: return hipErrorInvalidValue;
   }
 }

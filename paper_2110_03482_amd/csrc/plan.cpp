@@ -22,6 +22,7 @@ namespace {
 thread_local std::string g_last_error;
 
 constexpr size_t kAlign = 256;
+constexpr int kGridMinTrials = 64;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 bool mul_ok(size_t a, size_t b, size_t* out) {
@@ -167,6 +168,136 @@ static void linear_table(const fdd_plan_s* p, std::vector<uint4>* out) {
   }
 }
 
+void grid_order(const fdd_plan_s* p, std::vector<int>* out) {
+  out->resize(p->kappa.size());
+  for (size_t c = 0; c < out->size(); ++c) (*out)[c] = (int)c;
+  std::stable_sort(out->begin(), out->end(), [&](int x, int y) { return p->kappa[(size_t)x] < p->kappa[(size_t)y]; });
+}
+
+void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out) {
+  const size_t nc = p->kappa.size();
+  std::vector<int> order;
+  grid_order(p, &order);
+  out->resize((size_t)r.n_blk * nc);
+  for (int b = 0; b < r.n_blk; ++b) {
+    const double centre = r.dm0 + (double)(b * r.blk + r.blk / 2) * r.step;
+    for (size_t c = 0; c < nc; ++c) {
+      uint4 e;
+      const double kap = p->kappa[(size_t)order[c]];
+      turn_fraction(r.step * kap, p->log_len, &e.x, &e.y);
+      turn_fraction(centre * kap, p->log_len, &e.z, &e.w);
+      (*out)[(size_t)b * nc + c] = e;
+    }
+  }
+}
+
+// Whether the grid kernel is faster than the plan's kernel family, by times per unit of work.
+// The grid: a workgroup round (4 bins, one column group) costs a fixed part (two transforms, their
+// exchange and the hand-over) and a part per schedule step; the schedule of a bin is shared by
+// its column groups.  The families: useful flops of the matrix product at the measured rates, with
+// the chunk columns padded to a tile of 8 for the direct kernels.
+static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& runs) {
+  constexpr double kRoundUs = 10.5, kStepUs = 0.75, kBatchUs = 1.1, kStartUs = 8.0;
+  const int n_chan = p->desc.n_chan;
+  double grid = 0.0, direct = 0.0;
+  const bool fp32 = p->desc.precision == FDD_FP32;
+  const bool fac = p->fac_fine > 0 && p->facw_nt == 0;
+  // TFLOP/s of the family
+  const double rate = p->facw_nt > 0 ? 270.0 : fac ? (fp32 ? 90.0 : 150.0) : p->kernel == "valu" ? 8.0 : fp32 ? 100.0 : 190.0;
+  const int cols = p->facw_nt > 0 || fac || p->kernel == "valu" ? N : (N + 7) / 8 * 8;
+  for (const GridRun& r : runs) {
+    const double bins = (double)(p->L / p->segs[(size_t)r.seg].factor / 2 + 1);
+    const int lm = 1 << (r.log_m - 6), per = 64 / lm;
+    const double its = (double)((N + per - 1) / per) * r.n_blk;
+    const double rounds = std::ceil(std::ceil(bins / 4.0) * its / (double)kGridBlocks);
+    const double setups = std::max(1.0, std::ceil(bins / 4.0) * r.n_blk / (double)kGridBlocks);
+    grid += kStartUs + rounds * (kRoundUs + kStepUs * (double)((n_chan + lm - 1) / lm)) +
+            setups * kBatchUs * (double)((n_chan + 63) / 64);
+    direct += 8.0 * (double)r.n * (double)n_chan * bins * (double)cols / (rate * 1e6);
+  }
+  return grid < direct;
+}
+
+// The plan's trials as runs of equal steps (as uniform_grid tests them), each inside one segment;
+// false if a run is too short for the grid kernel or the plan's delays are rounded.
+bool grid_runs(const fdd_plan_s* p, int N, std::vector<GridRun>* out) {
+  out->clear();
+  if (p->desc.delay_mode != FDD_DELAY_EXACT) return false;
+  double big = 0.0;
+  for (double v : p->dms) big = std::max(big, std::fabs(v));
+  const double tol = 1e-12 * big;
+  for (size_t s = 0; s < p->segs.size(); ++s) {
+    const Segment& sg = p->segs[s];
+    for (int j = sg.j0; j < sg.j0 + sg.n;) {
+      // the longest run from j whose trials lie on the line through its first and last one
+      int n = 1;
+      const int left = sg.j0 + sg.n - j;
+      const double* d = p->dms.data() + j;
+      auto straight = [&](int m) {
+        const double st = (d[m - 1] - d[0]) / (double)(m - 1);
+        if (!(st > 0.0)) return false;
+        for (int i = 1; i < m - 1; ++i)
+          if (std::fabs(d[i] - (d[0] + (double)i * st)) > tol) return false;
+        return true;
+      };
+      if (left >= 2 && straight(left)) {
+        n = left;
+      } else {
+        while (n < left && d[n] > d[n - 1] && (n < 2 || std::fabs(d[n] - 2.0 * d[n - 1] + d[n - 2]) <= tol)) ++n;
+        while (n > 1 && !straight(n)) --n;
+      }
+      if (n < kGridMinTrials) {
+        out->clear();
+        return false;
+      }
+      GridRun r;
+      r.seg = (int)s;
+      r.j0 = j;
+      r.n = n;
+      r.dm0 = d[0];
+      r.step = (d[n - 1] - d[0]) / (double)(n - 1);
+      // one step moves no channel by L samples or more, so the turns per bin are a fraction
+      double kmin = p->kappa[0], kmax = p->kappa[0];
+      for (double k : p->kappa) {
+        kmin = std::min(kmin, k);
+        kmax = std::max(kmax, k);
+      }
+      if (!(r.step * kmax < 0.5 * (double)p->L)) {
+        out->clear();
+        return false;
+      }
+      uint32_t lo = 0, hi = 0;
+      turn_fraction(r.step * kmin, p->log_len, &lo, &hi);
+      r.inc_min = ((uint64_t)hi << 32) | lo;
+      turn_fraction(r.step * kmax, p->log_len, &lo, &hi);
+      r.inc_max = ((uint64_t)hi << 32) | lo;
+      if (n > (1 << (kGridLogMax - 1))) {
+        r.log_m = kGridLogMax;
+        r.n_blk = (n + (1 << (kGridLogMax - 1)) - 1) >> (kGridLogMax - 1);
+        r.blk = (n + r.n_blk - 1) / r.n_blk;
+      } else {
+        // a wave takes 2^(12 - log_m) chunks at once: the largest grid that leaves no more idle
+        r.n_blk = 1;
+        r.blk = n;
+        int need = kGridLogMin;
+        while ((1 << need) < 2 * n) ++need;
+        int best = 0;
+        for (int lg = need; lg <= kGridLogMax; ++lg) {
+          const int per = 1 << (kGridLogMax - lg), groups = (N + per - 1) / per;
+          if (best == 0 || groups <= best) {
+            best = groups;
+            r.log_m = lg;
+          }
+        }
+      }
+      out->push_back(r);
+      j += n;
+    }
+  }
+  if (!p->grid_force && !grid_pays(p, N, *out)) out->clear();
+  return !out->empty();
+}
+
 // Nearest-sample delays d = floor(tau + 1/2) of every (channel, DM), channel-major.
 static void delay_table(const fdd_plan_s* p, std::vector<int>* out) {
   const size_t nc = p->kappa.size(), nd = p->dms.size();
@@ -194,7 +325,9 @@ static void build_host_tables(fdd_plan_s* p) {
     keep(sg.tw, tw.data(), tw.size() * sizeof(float2));
   }
   std::vector<uint4> tab;
-  if (p->fac_fine > 0) {
+  if (!p->grid.empty() && !p->scaled) {
+    // no phase table
+  } else if (p->fac_fine > 0) {
     factor_tables(p, p->fac_fine, p->fac_coarse, p->fac_dm0, p->fac_step, &tab);
   } else {
     std::vector<uint4> part;
@@ -203,7 +336,12 @@ static void build_host_tables(fdd_plan_s* p) {
       tab.insert(tab.end(), part.begin(), part.end());
     }
   }
-  keep(w.ptab, tab.data(), tab.size() * sizeof(uint4));
+  if (!tab.empty()) keep(w.ptab, tab.data(), tab.size() * sizeof(uint4));
+  if (!p->grid.empty()) {
+    std::vector<int> order;
+    grid_order(p, &order);
+    keep(w.grid, order.data(), order.size() * sizeof(int));
+  }
   std::vector<int> dt;
   delay_table(p, &dt);
   keep(w.dtab, dt.data(), w.dtab_bytes);
@@ -212,6 +350,14 @@ static void build_host_tables(fdd_plan_s* p) {
     scaled_table(p, &ct);
     keep(w.ctab, ct.data(), w.ctab_bytes);
     keep(w.dmv, p->dms.data(), w.dmv_bytes);
+  }
+  for (const GridRun& r : p->grid) {
+    std::vector<uint4> ct;
+    grid_table(p, r, &ct);
+    keep(r.ctab, ct.data(), ct.size() * sizeof(uint4));
+    std::vector<float> dv;
+    grid_divisors(r.log_m, &dv);
+    keep(r.dec, dv.data(), dv.size() * sizeof(float));
   }
   if (p->lin) {
     std::vector<uint4> lt;
@@ -272,7 +418,15 @@ static fdd_status layout(fdd_plan_s* p) {
   const size_t rows_tab = std::max((size_t)d.n_dm, (size_t)p->fac_coarse + (size_t)p->fac_fine);
   if (!mul_ok((size_t)d.n_chan * rows_tab, sizeof(uint4), &w.ptab_bytes))
     return fail(FDD_E_NOMEM, "phase table size overflows");
+  if (!p->grid.empty()) {
+    // the grid kernel reads no phase table: its schedules take that space, unless the plan's
+    // scaled-DM spectra need the table for their lowest bins
+    w.sched_bytes = (size_t)kGridBlocks * 4 * (size_t)grid_sched_len(d.n_chan) * sizeof(uint4);
+    if (!p->scaled) w.ptab_bytes = std::max(w.ptab_bytes, w.sched_bytes);
+  }
   put(&w.ptab, w.ptab_bytes);
+  w.sched = w.ptab;
+  if (!p->grid.empty() && p->scaled) put(&w.sched, w.sched_bytes);
   w.scale_bytes = (size_t)p->n_chunks * sizeof(float);
   put(&w.scale, w.scale_bytes);
   if (d.input == FDD_IN_U8_TIME_MAJOR) {
@@ -305,6 +459,14 @@ static fdd_status layout(fdd_plan_s* p) {
   if (!mul_ok((size_t)d.n_chan * (size_t)d.n_dm, sizeof(int), &w.dtab_bytes))
     return fail(FDD_E_NOMEM, "delay table size overflows");
   put(&w.dtab, w.dtab_bytes);
+  if (!p->grid.empty()) {
+    put(&w.grid, (size_t)d.n_chan * sizeof(int));
+    for (GridRun& r : p->grid) {
+      put(&r.ctab, (size_t)r.n_blk * (size_t)d.n_chan * sizeof(uint4));
+      put(&r.dec, (sizeof(float) << (r.log_m - 1)));
+    }
+    w.grid_bytes = off - w.grid;
+  }
   if (p->lin) {
     w.ltab_bytes = (size_t)d.n_chan * sizeof(uint4);
     put(&w.ltab, w.ltab_bytes);
@@ -577,6 +739,15 @@ fdd_status fdd_plan(const fdd_plan_desc* desc, fdd_plan_t* out) {
       p->grid_step = step;
     }
   }
+  // The grid form of the phasor sum (FDD_GRID=0: never, 1: wherever it applies).  A kernel family
+  // asked for by name keeps its own kernels.
+  {
+    const char* ge = std::getenv("FDD_GRID");
+    const bool off = (ge != nullptr && std::strcmp(ge, "0") == 0) || std::getenv("FDD_FACTOR") != nullptr ||
+                     std::getenv("FDD_TILE_VARIANT") != nullptr || std::getenv("FDD_PHASE_TABLE") != nullptr;
+    p->grid_force = ge != nullptr && std::strcmp(ge, "1") == 0;
+    if (!off) (void)grid_runs(p, (int)p->n_chunks, &p->grid);
+  }
   // spin-frequency-scaled DMs (Eq. 8): first block whose rows stay within the halo
   if (d.flags & FDD_PLAN_SCALED_DM) {
     double dm0 = 0.0, step = 0.0;
@@ -619,6 +790,16 @@ fdd_status fdd_plan(const fdd_plan_desc* desc, fdd_plan_t* out) {
     (tile == tdd_dm_tile() ? p->tdd_span : p->tdd_span64) = span;
   }
   fdd_status st = layout(p);
+  if (st == FDD_OK && !p->grid.empty() && p->ws.total > kNoallocScratchBytes) {
+    // a plan that fits the static scratch of fdd_execute_noalloc without the schedules keeps fitting
+    std::vector<GridRun> runs;
+    runs.swap(p->grid);
+    st = layout(p);
+    if (st == FDD_OK && p->ws.total > kNoallocScratchBytes) {
+      runs.swap(p->grid);
+      st = layout(p);
+    }
+  }
   if (st != FDD_OK) {
     delete p;
     return st;
@@ -686,6 +867,15 @@ fdd_status fdd_plan_factors(fdd_plan_t p, int32_t* fine, int32_t* coarse, int32_
   if (fine != nullptr) *fine = p->fac_fine;
   if (coarse != nullptr) *coarse = p->fac_coarse;
   if (col_tiles != nullptr) *col_tiles = p->facw_nt;
+  return FDD_OK;
+}
+
+fdd_status fdd_plan_grid(fdd_plan_t p, int32_t* n_runs, int32_t* points) {
+  if (p == nullptr) return fail(FDD_E_INVALID, "null plan");
+  int most = 0;
+  for (const GridRun& r : p->grid) most = std::max(most, 1 << r.log_m);
+  if (n_runs != nullptr) *n_runs = (int32_t)p->grid.size();
+  if (points != nullptr) *points = (int32_t)most;
   return FDD_OK;
 }
 
