@@ -267,10 +267,9 @@ hipError_t launch_grid_stack(const fdd_batch_s* b, const Stack& sk, hipStream_t 
     a.ctab = (const uint4*)(b->d_tab + r.ctab);
     a.dec = (const float*)(b->d_tab + r.dec);
     a.perm = (const int*)(b->d_tab + sk.perm);
-    a.sched = (uint4*)(b->d_tab + b->sched);
-    a.sched_len = grid_sched_len(p->desc.n_chan);
     a.inc_min = r.inc_min;
     a.inc_max = r.inc_max;
+    std::copy(std::begin(r.gap), std::end(r.gap), a.gap);
     a.Yc = (float2*)(scr + sk.Yr) + (size_t)r.j0 * (size_t)sk.n_chunks * (size_t)p->pitch;
     a.n_dm = r.n;
     a.n_chan = p->desc.n_chan;
@@ -278,8 +277,11 @@ hipError_t launch_grid_stack(const fdd_batch_s* b, const Stack& sk, hipStream_t 
     a.log_m = r.log_m;
     a.blk = r.blk;
     a.n_blk = r.n_blk;
+    a.log_gb = r.log_gb;
+    a.window = r.window;
     a.n_bins = (int)p->n_bins;
     a.pitch = p->pitch;
+    grid_set_scratch(&a, b->d_tab + b->sched, p->desc.n_chan, p->n_bins);
     const hipError_t e = launch_phasor_grid(a, st);
     if (e != hipSuccess) return e;
   }
@@ -691,7 +693,7 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
         r.dec = off;
         off = align_up(off + (sizeof(float) << (r.log_m - 1)));
       }
-      sched_bytes = std::max(sched_bytes, (size_t)kGridBlocks * 4 * (size_t)grid_sched_len(p->desc.n_chan) * sizeof(uint4));
+      for (const GridRun& r : sk.grid) sched_bytes = std::max(sched_bytes, grid_scratch_bytes(p, r));
       continue;
     }
     sk.tab = off;

@@ -112,10 +112,9 @@ hipError_t launch_grid_run(fdd_plan_t p, const GridRun& r, const PhasorArgs& all
   a.ctab = (const uint4*)(p->d_ws + r.ctab);
   a.dec = (const float*)(p->d_ws + r.dec);
   a.perm = (const int*)(p->d_ws + p->ws.grid);
-  a.sched = (uint4*)(p->d_ws + p->ws.sched);
-  a.sched_len = grid_sched_len(s.n_chan);
   a.inc_min = r.inc_min;
   a.inc_max = r.inc_max;
+  std::copy(std::begin(r.gap), std::end(r.gap), a.gap);
   if (power) a.P = s.P + row * (size_t)s.n_pow_bins;
   else a.Yc = s.Yc + row * (size_t)s.n_chunks * (size_t)s.pitch;
   a.n_dm = r.n;
@@ -124,10 +123,13 @@ hipError_t launch_grid_run(fdd_plan_t p, const GridRun& r, const PhasorArgs& all
   a.log_m = r.log_m;
   a.blk = r.blk;
   a.n_blk = r.n_blk;
+  a.log_gb = r.log_gb;
+  a.window = r.window;
   a.n_bins = s.n_bins;
   a.n_pow_bins = s.n_pow_bins;
   a.pitch = s.pitch;
   a.dc_add = s.dc_add;
+  grid_set_scratch(&a, p->d_ws + p->ws.sched, s.n_chan, p->L / p->segs[(size_t)r.seg].factor / 2 + 1);
   return launch_phasor_grid(a, st);
 }
 

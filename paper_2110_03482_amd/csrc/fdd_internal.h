@@ -93,14 +93,21 @@ struct PhasorArgs {
 
 // Phasor sum of equally spaced trials with exact delays as a non-uniform Fourier transform along
 // the trial axis: n_blk blocks of blk trials, each on a grid of 2^log_m >= 2 blk points.
+constexpr int kGridGaps = 8;
+constexpr int kGridGuard = 8;       // grid points by which a channel may move within the bins of an order
 struct GridArgs {
   const float2* X = nullptr;        // [n_chan][n_chunks][pitch]
   const uint4* ctab = nullptr;      // [n_blk][n_chan] {turns per bin of one DM step (lo, hi), of the
                                     // block's centre trial blk / 2 (lo, hi)}
   const int* perm = nullptr;        // [n_chan] channel of each table entry (entries by ascending delay)
-  uint4* sched = nullptr;           // scratch, sched_len entries per wave of the launch
+  uint4* sched = nullptr;           // scratch: schedules of the launch's waves,
+  uint16_t* places = nullptr;       // [groups of bins][sched_len] orders of the channels,
+  int* turns = nullptr;             // [groups of bins], and
+  float4* dump = nullptr;           // 16 bytes per lane that nobody reads
   int sched_len = 0;
   uint64_t inc_min = 0, inc_max = 0; // smallest and largest turns per bin of one DM step
+  uint64_t gap[kGridGaps] = {};     // smallest difference of the turns of channels 2^j parts of the
+                                    // order apart (a part: half a lane's share of the channels); ~0: none
   const float* dec = nullptr;       // [2^(log_m - 1)] row divisors (reciprocals)
   float2* Yc = nullptr;             // [n_dm][n_chunks][pitch] complex, or
   float* P = nullptr;               // [n_dm][n_pow_bins] power spectra (one chunk)
@@ -110,6 +117,8 @@ struct GridArgs {
   int log_m = 0;
   int blk = 0;
   int n_blk = 0;
+  int log_gb = 0;                   // 2^log_gb bins share one order of the channels
+  int window = 2;                   // buckets of 8 points that keep two channels of a step apart
   int n_bins = 0;
   int n_pow_bins = 0;
   int64_t pitch = 0;
@@ -319,9 +328,25 @@ FacwChoice facw_choose(int n_dm, int n_chunks);
 hipError_t launch_phasor_facw(const PhasorArgs& a, int precision, int nt, hipStream_t st);
 // The non-uniform transform along the trial axis, and its row divisors.
 constexpr int kGridLogMin = 8, kGridLogMax = 12;   // grid points per column, 2^8 .. 2^12
-constexpr int kGridBlocks = 256;                    // workgroups of a launch at most (one per CU)
+constexpr int kGridWaves = 1024;                    // waves of a launch at most (four per CU)
 // Schedule entries per wave: every channel once, in equal parts per lane.
-inline int grid_sched_len(int n_chan) { return (n_chan + 63) / 64 * 64; }
+inline int grid_sched_len(int n_chan) { return (n_chan + 127) / 128 * 128; }
+inline int64_t grid_groups(int64_t n_bins, int log_gb) { return (n_bins + (int64_t(1) << log_gb) - 1) >> log_gb; }
+// Scratch of a launch: the schedules (an entry per channel and wave), the dump, then per group of
+// bins the turns and the places.
+inline size_t grid_sched_bytes(int n_chan) {
+  return (size_t)kGridWaves * ((size_t)grid_sched_len(n_chan) * sizeof(uint4) + 64 * sizeof(float4));
+}
+inline size_t grid_order_bytes(int n_chan, int64_t n_bins, int log_gb) {
+  return (size_t)grid_groups(n_bins, log_gb) * (sizeof(int) + (size_t)grid_sched_len(n_chan) * sizeof(uint16_t));
+}
+inline void grid_set_scratch(GridArgs* a, uint8_t* mem, int n_chan, int64_t n_bins) {
+  a->sched_len = grid_sched_len(n_chan);
+  a->sched = (uint4*)mem;
+  a->dump = (float4*)(a->sched + (size_t)kGridWaves * (size_t)a->sched_len);
+  a->turns = (int*)(mem + grid_sched_bytes(n_chan));
+  a->places = (uint16_t*)(a->turns + grid_groups(n_bins, a->log_gb));
+}
 hipError_t launch_phasor_grid(const GridArgs& a, hipStream_t st);
 void grid_divisors(int log_m, std::vector<float>* out);
 // Spin-frequency-scaled DMs: the per-block matrix products and the resampling in DM.
@@ -365,8 +390,10 @@ struct GridRun {
   int j0 = 0, n = 0;                  // trials j0 .. j0 + n - 1 of the plan
   double dm0 = 0.0, step = 0.0;       // DM of trial j0, and the step
   int log_m = 0, blk = 0, n_blk = 0;
+  int log_gb = 0, window = 2;         // GridArgs
   size_t ctab = 0, dec = 0;           // workspace byte offsets
   uint64_t inc_min = 0, inc_max = 0;  // smallest and largest turns per bin of one step
+  uint64_t gap[kGridGaps] = {};       // GridArgs::gap
 };
 
 struct WorkspaceLayout {
@@ -445,6 +472,7 @@ void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out);
 // The plan's trials as grid runs for n_chunks chunks; false if they have no such form or the kernel
 // family of the plan is the faster one.
 bool grid_runs(const fdd_plan_s* p, int n_chunks, std::vector<GridRun>* out);
+size_t grid_scratch_bytes(const fdd_plan_s* p, const GridRun& r);
 // Channels by ascending delay.
 void grid_order(const fdd_plan_s* p, std::vector<int>* out);
 // Enqueue the copies of the plan's host tables into a workspace at dst (same layout) on st.

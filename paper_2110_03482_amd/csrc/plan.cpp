@@ -23,6 +23,7 @@ thread_local std::string g_last_error;
 
 constexpr size_t kAlign = 256;
 constexpr int kGridMinTrials = 64;
+constexpr int kGridLogOrder = 10;   // bins of one order at most
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
 bool mul_ok(size_t a, size_t b, size_t* out) {
@@ -191,31 +192,53 @@ void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out) 
   }
 }
 
-// Whether the grid kernel is faster than the plan's kernel family, by times per unit of work.
-// The grid: a workgroup round (4 bins, one column group) costs a fixed part (two transforms, their
-// exchange and the hand-over) and a part per schedule step; the schedule of a bin is shared by
-// its column groups.  The families: useful flops of the matrix product at the measured rates, with
-// the chunk columns padded to a tile of 8 for the direct kernels.
+// Whether the grid kernel is expected to be faster than the plan's family: a model of both, from
+// measured times of 260 shapes (4096 to 65536 samples a chunk, 1 to 20 chunks, 32 to 1024 channels,
+// 64 to 2048 trials).  The grid kernel: a column group (its transform, stores and up to 8 or 16
+// spread steps) costs kRoundUs and runs on 512 workgroups at a time, more steps cost kStepUs each on
+// top of a base without staged values, and the entries of a bin kBatchUs per 64 channels; it
+// predicts the measured times within -25 and +30 %.  The direct families: their best measured rates
+// over the work that they really do (whole tiles of trials and columns), so the line lies where the
+// grid wins with the direct kernel at its best.  E.g. 8192 samples, 20 chunks: 200 channels and 256
+// trials 384 us against 449 us (mfma_f32), 128 channels and 128 trials 237 against 161; one chunk of
+// 65536, 2048 trials: 128 channels 468 against 772 us (fac_f32), 64 channels 445 against 445.
 static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& runs) {
-  constexpr double kRoundUs = 10.5, kStepUs = 0.75, kBatchUs = 1.1, kStartUs = 8.0;
+  constexpr double kRoundUs[2] = {12.9, 17.7}, kBaseUs = 11.6, kStepUs = 0.467, kBatchUs = 0.266, kStartUs = 11.0;
+  constexpr double kBlocks = 512.0;
   const int n_chan = p->desc.n_chan;
   double grid = 0.0, direct = 0.0;
   const bool fp32 = p->desc.precision == FDD_FP32;
   const bool fac = p->fac_fine > 0 && p->facw_nt == 0;
-  // TFLOP/s of the family
-  const double rate = p->facw_nt > 0 ? 270.0 : fac ? (fp32 ? 90.0 : 150.0) : p->kernel == "valu" ? 8.0 : fp32 ? 100.0 : 190.0;
-  const int cols = p->facw_nt > 0 || fac || p->kernel == "valu" ? N : (N + 7) / 8 * 8;
+  // TFLOP/s of the family, and its smallest tile of trials and channels
+  double rate = fp32 ? 100.0 : 140.0;
+  int dm_tile = 64, min_chan = 64, col_tile = 8;
+  if (p->facw_nt > 0) {
+    rate = 240.0, dm_tile = 128, min_chan = 96, col_tile = 1;
+  } else if (fac) {
+    rate = fp32 ? 92.0 : 170.0, dm_tile = 2048, min_chan = 1, col_tile = 1;
+  } else if (p->kernel == "valu") {
+    rate = 8.0, dm_tile = 1, min_chan = 1, col_tile = 1;
+  }
+  const auto up = [](int n, int to) { return (double)((n + to - 1) / to * to); };
   for (const GridRun& r : runs) {
     const double bins = (double)(p->L / p->segs[(size_t)r.seg].factor / 2 + 1);
     const int lm = 1 << (r.log_m - 6), per = 64 / lm;
+    const double pairs = std::ceil(bins / 2.0);
     const double its = (double)((N + per - 1) / per) * r.n_blk;
-    const double rounds = std::ceil(std::ceil(bins / 4.0) * its / (double)kGridBlocks);
-    const double setups = std::max(1.0, std::ceil(bins / 4.0) * r.n_blk / (double)kGridBlocks);
-    grid += kStartUs + rounds * (kRoundUs + kStepUs * (double)((n_chan + lm - 1) / lm)) +
-            setups * kBatchUs * (double)((n_chan + 63) / 64);
-    direct += 8.0 * (double)r.n * (double)n_chan * bins * (double)cols / (rate * 1e6);
+    const double rounds = std::ceil(pairs * its / kBlocks);
+    const double setups = std::max(1.0, std::ceil(pairs * r.n_blk / kBlocks));
+    const int steps = 2 * ((n_chan + 2 * lm - 1) / (2 * lm));
+    const double round = steps <= 8 ? kRoundUs[0] : steps <= 16 ? kRoundUs[1] : kBaseUs + kStepUs * steps;
+    grid += kStartUs + rounds * round + setups * kBatchUs * (double)((n_chan + 63) / 64);
+    direct += 6.0 + 8.0 * up(r.n, dm_tile) * (double)std::max(n_chan, min_chan) * bins * up(N, col_tile) / (rate * 1e6);
   }
   return grid < direct;
+}
+
+// Scratch of one run's launches.
+size_t grid_scratch_bytes(const fdd_plan_s* p, const GridRun& r) {
+  const int64_t bins = p->L / p->segs[(size_t)r.seg].factor / 2 + 1;
+  return grid_sched_bytes(p->desc.n_chan) + grid_order_bytes(p->desc.n_chan, bins, r.log_gb);
 }
 
 // The plan's trials as runs of equal steps (as uniform_grid tests them), each inside one segment;
@@ -226,6 +249,8 @@ bool grid_runs(const fdd_plan_s* p, int N, std::vector<GridRun>* out) {
   double big = 0.0;
   for (double v : p->dms) big = std::max(big, std::fabs(v));
   const double tol = 1e-12 * big;
+  std::vector<double> kap = p->kappa;
+  std::sort(kap.begin(), kap.end());
   for (size_t s = 0; s < p->segs.size(); ++s) {
     const Segment& sg = p->segs[s];
     for (int j = sg.j0; j < sg.j0 + sg.n;) {
@@ -257,20 +282,18 @@ bool grid_runs(const fdd_plan_s* p, int N, std::vector<GridRun>* out) {
       r.dm0 = d[0];
       r.step = (d[n - 1] - d[0]) / (double)(n - 1);
       // one step moves no channel by L samples or more, so the turns per bin are a fraction
-      double kmin = p->kappa[0], kmax = p->kappa[0];
-      for (double k : p->kappa) {
-        kmin = std::min(kmin, k);
-        kmax = std::max(kmax, k);
-      }
-      if (!(r.step * kmax < 0.5 * (double)p->L)) {
+      if (!(r.step * kap.back() < 0.5 * (double)p->L)) {
         out->clear();
         return false;
       }
-      uint32_t lo = 0, hi = 0;
-      turn_fraction(r.step * kmin, p->log_len, &lo, &hi);
-      r.inc_min = ((uint64_t)hi << 32) | lo;
-      turn_fraction(r.step * kmax, p->log_len, &lo, &hi);
-      r.inc_max = ((uint64_t)hi << 32) | lo;
+      std::vector<uint64_t> inc(kap.size());
+      for (size_t c = 0; c < kap.size(); ++c) {
+        uint32_t lo = 0, hi = 0;
+        turn_fraction(r.step * kap[c], p->log_len, &lo, &hi);
+        inc[c] = ((uint64_t)hi << 32) | lo;
+      }
+      r.inc_min = inc.front();
+      r.inc_max = inc.back();
       if (n > (1 << (kGridLogMax - 1))) {
         r.log_m = kGridLogMax;
         r.n_blk = (n + (1 << (kGridLogMax - 1)) - 1) >> (kGridLogMax - 1);
@@ -289,6 +312,21 @@ bool grid_runs(const fdd_plan_s* p, int N, std::vector<GridRun>* out) {
             r.log_m = lg;
           }
         }
+      }
+      // The bins that share one order lie within half of their number of its bin: there a channel
+      // moves by inc M grid points per bin, which has to stay within the guard, and two channels
+      // towards each other by the difference of theirs.
+      const double points = std::ldexp(1.0, r.log_m - 64);
+      r.log_gb = 0;
+      while (r.log_gb < kGridLogOrder && (double)(1 << r.log_gb) * (double)r.inc_max * points <= (double)(kGridGuard - 1)) ++r.log_gb;
+      const double half = r.log_gb > 0 ? (double)(1 << (r.log_gb - 1)) : 0.0;
+      r.window = 2 + (int)std::ceil(half * (double)(r.inc_max - r.inc_min) * points / 8.0);
+      const int lm = 1 << (r.log_m - 6);
+      const size_t part = (kap.size() + 2 * (size_t)lm - 1) / (2 * (size_t)lm);
+      for (int g = 0; g < kGridGaps; ++g) {
+        const size_t d = part << g;
+        r.gap[g] = ~uint64_t(0);
+        for (size_t c = 0; c + d < inc.size(); ++c) r.gap[g] = std::min(r.gap[g], inc[c + d] - inc[c]);
       }
       out->push_back(r);
       j += n;
@@ -421,7 +459,8 @@ static fdd_status layout(fdd_plan_s* p) {
   if (!p->grid.empty()) {
     // the grid kernel reads no phase table: its schedules take that space, unless the plan's
     // scaled-DM spectra need the table for their lowest bins
-    w.sched_bytes = (size_t)kGridBlocks * 4 * (size_t)grid_sched_len(d.n_chan) * sizeof(uint4);
+    w.sched_bytes = 0;
+    for (const GridRun& r : p->grid) w.sched_bytes = std::max(w.sched_bytes, grid_scratch_bytes(p, r));
     if (!p->scaled) w.ptab_bytes = std::max(w.ptab_bytes, w.sched_bytes);
   }
   put(&w.ptab, w.ptab_bytes);

@@ -47,6 +47,8 @@ CASES = [(64, 4096, 64, 4096, True, "f32", 20.0, (1.0,)),          # one column,
          (100, 30000, 512, 4096, False, "u8", 12.0, (1.0,)),       # the most trials of 2^10 points
          (40, 30000, 600, 8192, False, "f32", 30.0, (1.0,)),       # 2^11 points
          (257, 12000, 1100, 4096, False, "f32", 9.0, (1.0,)),      # 2^12 points
+         (1024, 9000, 1030, 4096, False, "u8", 9.0, (1.0,)),       # the most channels whose values are staged
+         (1030, 4096, 1030, 4096, True, "f32", 9.0, (1.0,)),       # one part more: values read where they are used
          (33, 5000, 2049, 2048, False, "f32", 3.0, (1.0,)),        # two blocks of trials
          (48, 4096, 4500, 4096, True, "f32", 12.0, (1.0,)),        # three blocks, one chunk
          (1, 5000, 70, 2048, False, "f32", 3.0, (1.0,)),           # one channel
