@@ -43,7 +43,7 @@ struct LongPassArgs {
   const float2* in = nullptr;
   float2* out = nullptr;
   int64_t in_pitch = 0, out_pitch = 0;   // complex points between series
-  const uint8_t* in_u8 = nullptr;        // first forward pass: real input
+  const uint8_t* in_u8 = nullptr;        // forward: real input
   const float* in_f32 = nullptr;
   float* out_real = nullptr;             // last inverse pass: real output [row][n_samp]
   const float* yr = nullptr;             // inverse pre-split: Y planes

@@ -116,6 +116,50 @@ __device__ __forceinline__ void dft_reg(float2* a) {
   for (int k = 0; k < R; ++k) a[k] = t[k];
 }
 
+// u, t -> u + w t, u - w t with the second as 2 u - (u + w t): 6 fused operations.
+__device__ __forceinline__ void bfly(float2& u, float2& t, float wr, float wi) {
+  const float ar = fmaf(-wi, t.y, fmaf(wr, t.x, u.x));
+  const float ai = fmaf(wi, t.x, fmaf(wr, t.y, u.y));
+  t = make_float2(fmaf(2.0f, u.x, -ar), fmaf(2.0f, u.y, -ai));
+  u = make_float2(ar, ai);
+}
+
+// Stages LOGB .. LOG2(R) of a decimation-in-time transform with sign -1 or +1 (INV), in place on x
+// (bit-reversed order in, natural order out): stage s joins blocks of 2^(s-1).  A butterfly is 6
+// operations and rounds each value twice; dft_reg's takes 8 and rounds up to three times.
+template <int R, int LOGB, bool INV>
+__device__ __forceinline__ void dit_stages(float2* x) {
+  constexpr RootTable<R, INV> tab{};
+#pragma unroll
+  for (int half = 1 << (LOGB - 1); half < R; half *= 2) {
+#pragma unroll
+    for (int s = 0; s < R; s += 2 * half) {
+#pragma unroll
+      for (int j = 0; j < half; ++j) {
+        float2& u = x[s + j];
+        float2& t = x[s + j + half];
+        const int m = j * (R / (2 * half));          // exp(-/+ 2 pi i m / R)
+        if (m == 0) {
+          const float2 d = f2sub(u, t);
+          u = f2add(u, t);
+          t = d;
+        } else if (4 * m == R) {                     // -/+ i t
+          const float2 p = make_float2(u.x - t.y, u.y + t.x), n = make_float2(u.x + t.y, u.y - t.x);
+          u = INV ? p : n;
+          t = INV ? n : p;
+        } else if (2 * half == R) {                  // last stage: outputs that nobody reads drop out one by one
+          const float c = tab.c[m], sn = tab.s[m];
+          const float2 p = make_float2(fmaf(-sn, t.y, fmaf(c, t.x, u.x)), fmaf(sn, t.x, fmaf(c, t.y, u.y)));
+          t = make_float2(fmaf(sn, t.y, fmaf(-c, t.x, u.x)), fmaf(-sn, t.x, fmaf(-c, t.y, u.y)));
+          u = p;
+        } else {
+          bfly(u, t, tab.c[m], tab.s[m]);
+        }
+      }
+    }
+  }
+}
+
 __device__ __forceinline__ int lds_pad(int i) { return i + (i >> 5); }
 
 template <int LOGN>
@@ -154,6 +198,31 @@ __device__ __forceinline__ float2 rotate_const(float2 d) {
 
 __device__ __forceinline__ float2 cmulf(float2 a, float2 b) {
   return make_float2(fmaf(a.x, b.x, -a.y * b.y), fmaf(a.x, b.y, a.y * b.x));
+}
+
+// R-point DFT of v, sign -1 or +1 (INV), natural order in and out, as R1 x R2 points (4 x 4, 4 x 8,
+// 8 x 8): fewer multiplications than stage by stage, and so fewer roundings.
+template <int R, bool INV>
+__device__ __forceinline__ void dft_two(float2* v) {
+  constexpr int R1 = R >= 64 ? 8 : 4, R2 = R / R1;
+  float2 t[R];
+  static_for<0, R2>([&](auto ni) {
+    constexpr int n = decltype(ni)::value;
+    float2 a[R1];
+#pragma unroll
+    for (int i = 0; i < R1; ++i) a[cx_bitrev(i, cx_log2(R1))] = v[i * R2 + n];
+    dit_stages<R1, 1, INV>(a);
+    static_for<0, R1>([&](auto ki) {
+      constexpr int k = decltype(ki)::value;
+      t[k * R2 + cx_bitrev(n, cx_log2(R2))] = rotate_const<k * n, R, INV>(a[k]);
+    });
+  });
+#pragma unroll
+  for (int k = 0; k < R1; ++k) {
+    dit_stages<R2, 1, INV>(t + k * R2);
+#pragma unroll
+    for (int j = 0; j < R2; ++j) v[k + R1 * j] = t[k * R2 + j];
+  }
 }
 
 template <int LOGN, int LOGE, bool INV, int LOGRMAX = 4>

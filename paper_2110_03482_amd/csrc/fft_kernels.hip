@@ -308,18 +308,14 @@ __global__ __launch_bounds__(1 << (LOGN - LOGE)) void k_c2r_grouped(Group<FftArg
 
 // ----------------------------------------------------------------------------- long transforms
 //
-// Transforms longer than one workgroup can hold (N = L/2 > 2^15 complex points) run as a
-// sequence of global-memory Stockham passes, one radix-R butterfly per thread: butterfly j of
-// a series reads points j + r N/R (consecutive threads, consecutive addresses), applies the
-// twiddles exp(-/+ 2 pi i r k / (Ns R)), k = j mod Ns, and writes to the autosort positions
-// (j / Ns) Ns R + k + r Ns.  The first forward pass loads real samples directly (packing
-// x[2j] + i x[2j+1], zero point and zero padding as in k_r2c); the last inverse pass stores
-// real samples directly (scaling, valid-sample extraction and zero-point restore as in k_c2r).
-
-enum { kPassComplex = 0, kPassLoadF32 = 1, kPassLoadU8 = 2, kPassStoreReal = 3 };
-
-template <int LOGR, bool INV, int MODE>
-__global__ __launch_bounds__(256) void k_fft_pass(LongPassArgs a) {
+// Transforms longer than one workgroup can hold (N = L/2 > 2^15 complex points).  The forward ones
+// are below; the inverse ones run as a sequence of global-memory Stockham passes, one radix-R
+// butterfly per thread: butterfly j of a series reads points j + r N/R (consecutive threads,
+// consecutive addresses), applies the twiddles exp(2 pi i r k / (Ns R)), k = j mod Ns, and writes to
+// the autosort positions (j / Ns) Ns R + k + r Ns.  The last pass stores real samples directly
+// (scaling, valid-sample extraction and zero-point restore as in k_c2r).
+template <int LOGR, bool LAST>
+__global__ __launch_bounds__(256) void k_c2r_pass(LongPassArgs a) {
   constexpr int R = 1 << LOGR;
   const int64_t nb = (int64_t)1 << (a.log_n - LOGR);     // butterflies per series
   const int64_t j = (int64_t)blockIdx.x * 256 + threadIdx.x;
@@ -328,50 +324,20 @@ __global__ __launch_bounds__(256) void k_fft_pass(LongPassArgs a) {
   const int64_t Ns = (int64_t)1 << a.log_ns;
   const int64_t k = j & (Ns - 1);
   float2 v[R];
-  if constexpr (MODE == kPassLoadF32 || MODE == kPassLoadU8) {
-    const int row = series / a.n_chunks, chunk = series % a.n_chunks;
-    const int64_t s0 = (int64_t)chunk * a.stride;
-    const int64_t L = (int64_t)2 << a.log_n;
-    float zp = 0.0f;
-    float l1 = 0.0f;
-    if constexpr (MODE == kPassLoadU8) zp = (s0 + L <= a.n_samp) ? 128.0f : 0.0f;
+  const float2* src = a.in + (int64_t)series * a.in_pitch;
 #pragma unroll
-    for (int r = 0; r < R; ++r) {
-      const int64_t s = s0 + 2 * (j + r * nb);
-      float x0 = 0.0f, x1 = 0.0f;
-      if constexpr (MODE == kPassLoadU8) {
-        const uint8_t* src = a.in_u8 + (int64_t)row * a.n_samp;
-        if (s < a.n_samp) x0 = (float)src[s] - zp;
-        if (s + 1 < a.n_samp) x1 = (float)src[s + 1] - zp;
-      } else {
-        const float* src = a.in_f32 + (int64_t)row * a.n_samp;
-        if (s < a.n_samp) x0 = src[s];
-        if (s + 1 < a.n_samp) x1 = src[s + 1];
-      }
-      l1 += fabsf(x0) + fabsf(x1);
-      v[r] = make_float2(x0, x1);
-    }
-    if (a.l1sum != nullptr) {
-#pragma unroll
-      for (int o = 32; o >= 1; o >>= 1) l1 += __shfl_xor(l1, o, 64);
-      if ((threadIdx.x & 63) == 0) atomicAdd(a.l1sum + series, l1);
-    }
-  } else {
-    const float2* src = a.in + (int64_t)series * a.in_pitch;
-#pragma unroll
-    for (int r = 0; r < R; ++r) v[r] = src[j + r * nb];
-  }
+  for (int r = 0; r < R; ++r) v[r] = src[j + r * nb];
   if (a.log_ns > 0) {
-    // exp(-/+ 2 pi i r k / (Ns R)): angle r k / (Ns R) of a turn, exact in 32-bit fixed point
+    // exp(2 pi i r k / (Ns R)): angle r k / (Ns R) of a turn, exact in 32-bit fixed point
     const int sh = 32 - a.log_ns - LOGR;
     constexpr int G = R > 8 ? 8 : R;
     float2 lo[G];
 #pragma unroll
-    for (int vv = 1; vv < G; ++vv) lo[vv] = turn_phasor<INV>((uint32_t)(vv * k) << sh);
+    for (int vv = 1; vv < G; ++vv) lo[vv] = turn_phasor<true>((uint32_t)(vv * k) << sh);
 #pragma unroll
     for (int u = 0; u < R / G; ++u) {
       float2 hi = make_float2(1.0f, 0.0f);
-      if (u > 0) hi = turn_phasor<INV>((uint32_t)(u * G * k) << sh);
+      if (u > 0) hi = turn_phasor<true>((uint32_t)(u * G * k) << sh);
 #pragma unroll
       for (int vv = 0; vv < G; ++vv) {
         const int r = u * G + vv;
@@ -381,9 +347,9 @@ __global__ __launch_bounds__(256) void k_fft_pass(LongPassArgs a) {
       }
     }
   }
-  dft_reg<R, INV>(v);
+  dft_reg<R, true>(v);
   const int64_t base = ((j >> a.log_ns) << (a.log_ns + LOGR)) + k;
-  if constexpr (MODE == kPassStoreReal) {
+  if constexpr (LAST) {
     // point m holds samples 2m and 2m + 1 of the chunk
     const int row = series / a.n_chunks, chunk = series % a.n_chunks;
     const int64_t s0 = (int64_t)chunk * a.stride;
@@ -402,24 +368,6 @@ __global__ __launch_bounds__(256) void k_fft_pass(LongPassArgs a) {
 #pragma unroll
     for (int r = 0; r < R; ++r) dst[base + r * Ns] = v[r];
   }
-}
-
-// Real-to-complex split of a long series: X[f] for f = 0 .. N from Z[f] and Z[N - f].
-__global__ __launch_bounds__(256) void k_r2c_split(LongPassArgs a) {
-  const int64_t N = (int64_t)1 << a.log_n;
-  const int64_t f = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (f > N) return;
-  const int series = blockIdx.y;
-  const float2* z = a.in + (int64_t)series * a.in_pitch;
-  float2* x = a.out + (int64_t)series * a.out_pitch;
-  const float2 zf = z[f & (N - 1)];
-  const float2 zm = z[(N - f) & (N - 1)];
-  const float2 zc = make_float2(zm.x, -zm.y);
-  const float2 av = make_float2(0.5f * (zf.x + zc.x), 0.5f * (zf.y + zc.y));
-  const float2 d = make_float2(0.5f * (zf.x - zc.x), 0.5f * (zf.y - zc.y));
-  const float2 b = make_float2(d.y, -d.x);                                  // -i d
-  const float2 w = turn_phasor<false>((uint32_t)f << (31 - a.log_n));        // exp(-2 pi i f / L)
-  x[f] = make_float2(av.x + fmaf(w.x, b.x, -w.y * b.y), av.y + fmaf(w.x, b.y, w.y * b.x));
 }
 
 // Complex-to-real pre-split of a long series: Z[f] = A + i B from the planes of Y, scaled 1/N.
@@ -461,19 +409,210 @@ __global__ void k_zero_f32(float* p, int64_t n) {
   if (i < n) p[i] = 0.0f;
 }
 
+// Forward transforms of 2^16 .. 2^21 points take two passes over memory.  With n = N2 a + b and
+// bin = k1 + N1 k2 (N = N1 N2),
+//     A[k1][b] = sum_a z[N2 a + b] exp(-2 pi i a k1 / N1)                      (k_long_cols)
+//     Z[k1 + N1 k2] = sum_b A[k1][b] exp(-2 pi i b k1 / N) exp(-2 pi i b k2 / N2)   (k_long_rows)
+// and the second also makes the bins of the real series: conj Z[N - f] for f = k1 + N1 k2 is the same
+// sum over conj A[N1 - k1][b], with the same twiddles, so a thread that transforms the rows k1 and
+// N1 - k1 has both values that X[f] and X[N - f] are made of, in the same place.  Each transform of
+// up to 2048 points is two in-register ones with an exchange through LDS between them.
+// Bound: memory (the series once in, A once out and in, X once out).  512 series of 2^22 samples:
+// 24.1 ms as five passes of radix 16 and 32 and a split, 8.5 ms so (34.4 GB: 4.0 TB/s; a copy
+// reaches 4.75).
+constexpr int kLongCols = 16;                            // columns of a workgroup: 128 bytes of a row
+template <int LOGA>
+struct LongShape {
+  static constexpr int E = LOGA == 8 ? 16 : LOGA == 11 ? 64 : 32;   // points per thread: the first transform
+  static constexpr int T = (1 << LOGA) / E;              // threads per series: the second transform
+  static constexpr int NB = E / T;                       // second transforms per thread
+};
+
+// Point i of v, and of u if PAIR, times the phasor of -(base + i step) / 2^32 turns.  (Every phasor is
+// evaluated: with a quarter of them and products the transform took 8.0 instead of 8.3 ms, and 4 % more
+// error.)
+template <int E, bool PAIR>
+__device__ __forceinline__ void long_twiddle(float2* v, float2* u, uint32_t base, uint32_t step) {
+#pragma unroll
+  for (int i = 0; i < E; ++i) {
+    const float2 w = turn_phasor<false>(base + (uint32_t)i * step);
+    v[i] = cmulf(v[i], w);
+    if constexpr (PAIR) u[i] = cmulf(u[i], w);
+  }
+}
+
+template <int LOGA, bool U8>
+__global__ __launch_bounds__((kLongCols * LongShape<LOGA>::T)) void k_long_cols(LongPassArgs a) {
+  using S = LongShape<LOGA>;
+  constexpr int E = S::E, T = S::T, NB = S::NB, P = (E + 1) * kLongCols;
+  __shared__ float lds[T * P];
+  const int tid = (int)threadIdx.x, col = tid % kLongCols, t = tid / kLongCols;
+  const int series = (int)blockIdx.y, row = series / a.n_chunks, chunk = series % a.n_chunks;
+  const int log_b = a.log_n - LOGA;
+  const int64_t at = (int64_t)blockIdx.x * kLongCols + col;
+  const int64_t s0 = (int64_t)chunk * a.stride, L = (int64_t)2 << a.log_n;
+  const bool full = s0 + L <= a.n_samp;
+  float2 v[E];
+  if constexpr (U8) {
+    const float zp = full ? 128.0f : 0.0f;
+    const uint8_t* src = a.in_u8 + (int64_t)row * a.n_samp + s0;
+    if (full && ((uintptr_t)src & 1u) == 0) {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const uint32_t w = reinterpret_cast<const uint16_t*>(src)[at + ((int64_t)(t + T * e) << log_b)];
+        v[e] = make_float2((float)(w & 0xffu) - zp, (float)(w >> 8) - zp);
+      }
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int64_t s = 2 * (at + ((int64_t)(t + T * e) << log_b));
+        v[e].x = s0 + s < a.n_samp ? (float)src[s] - zp : 0.0f;
+        v[e].y = s0 + s + 1 < a.n_samp ? (float)src[s + 1] - zp : 0.0f;
+      }
+    }
+  } else {
+    const float* src = a.in_f32 + (int64_t)row * a.n_samp + s0;
+    if (full && ((uintptr_t)src & 7u) == 0) {
+#pragma unroll
+      for (int e = 0; e < E; ++e)
+        v[e] = reinterpret_cast<const float2*>(src)[at + ((int64_t)(t + T * e) << log_b)];
+    } else {
+#pragma unroll
+      for (int e = 0; e < E; ++e) {
+        const int64_t s = 2 * (at + ((int64_t)(t + T * e) << log_b));
+        v[e].x = s0 + s < a.n_samp ? src[s] : 0.0f;
+        v[e].y = s0 + s + 1 < a.n_samp ? src[s + 1] : 0.0f;
+      }
+    }
+  }
+  if (a.l1sum != nullptr) {
+    float l1 = 0.0f;
+#pragma unroll
+    for (int e = 0; e < E; ++e) l1 += fabsf(v[e].x) + fabsf(v[e].y);
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) l1 += __shfl_xor(l1, o, 64);
+    if ((tid & 63) == 0) atomicAdd(a.l1sum + series, l1);
+  }
+  dft_two<E, false>(v);
+  long_twiddle<E, false>(v, nullptr, 0u, (uint32_t)t << (32 - LOGA));
+#pragma unroll
+  for (int part = 0; part < 2; ++part) {
+#pragma unroll
+    for (int k = 0; k < E; ++k) lds[t * P + k * kLongCols + col] = part ? v[k].y : v[k].x;
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < NB; ++m)
+#pragma unroll
+      for (int j = 0; j < T; ++j) {
+        const float x = lds[j * P + (t + T * m) * kLongCols + col];
+        if (part) v[m * T + j].y = x;
+        else v[m * T + j].x = x;
+      }
+    if (part == 0) __syncthreads();
+  }
+  float2* dst = a.out + (int64_t)series * a.out_pitch + at;
+#pragma unroll
+  for (int m = 0; m < NB; ++m) {
+    dft_two<T, false>(v + m * T);
+#pragma unroll
+    for (int j = 0; j < T; ++j) dst[(int64_t)(t + T * m + E * j) << log_b] = v[m * T + j];
+  }
+}
+
+// Pairs of rows (k1, N1 - k1) of a workgroup: their bins lie side by side in X.
+constexpr int kLongPairs = 16;
+template <int LOGB>
+__global__ __launch_bounds__((kLongPairs * LongShape<LOGB>::T)) void k_long_rows(LongPassArgs a, int n_tile) {
+  using S = LongShape<LOGB>;
+  constexpr int E = S::E, T = S::T, NB = S::NB, PT = E + 1;
+  constexpr int PP = T * PT + 4;                          // 4 times an odd number, modulo 64: the reads fall in 64 banks
+  static_assert(PP / 4 % 2 == 1, "bank layout");
+  __shared__ float lds[kLongPairs * PP];
+  const int tid = (int)threadIdx.x;
+  const int log_a = a.log_n - LOGB;
+  const int n1 = 1 << log_a;
+  // neighbouring tiles share lines of X: they go to one XCD, one after the other
+  const int per = (n_tile + 7) / 8;
+  const int tile = (int)blockIdx.x % 8 * per + (int)blockIdx.x / 8;
+  if (tile >= n_tile) return;
+  const int k0 = tile * kLongPairs;
+  const float2* src = a.in + (int64_t)blockIdx.y * a.in_pitch;
+  float2 v[E], u[E];
+  {
+    const int t = tid % T, p = tid / T;
+    const int k1 = min(k0 + p, n1 / 2), km = (n1 - k1) & (n1 - 1);
+    const float2* r0 = src + ((int64_t)k1 << LOGB) + t;
+    const float2* r1 = src + ((int64_t)km << LOGB) + t;
+#pragma unroll
+    for (int e = 0; e < E; ++e) {
+      v[e] = r0[T * e];
+      u[e] = r1[T * e];
+    }
+#pragma unroll
+    for (int e = 0; e < E; ++e) u[e].y = -u[e].y;
+    const int sh = 32 - a.log_n;
+    long_twiddle<E, true>(v, u, (uint32_t)(t * k1) << sh, (uint32_t)(T * k1) << sh);
+    dft_two<E, false>(v);
+    dft_two<E, false>(u);
+    long_twiddle<E, true>(v, u, 0u, (uint32_t)t << (32 - LOGB));
+  }
+  const int wt = tid % T, wp = tid / T, p = tid % kLongPairs, t = tid / kLongPairs;
+  auto swap = [&](float2* z, bool more) {
+#pragma unroll
+    for (int part = 0; part < 2; ++part) {
+#pragma unroll
+      for (int k = 0; k < E; ++k) lds[wp * PP + wt * PT + k] = part ? z[k].y : z[k].x;
+      __syncthreads();
+#pragma unroll
+      for (int m = 0; m < NB; ++m)
+#pragma unroll
+        for (int j = 0; j < T; ++j) {
+          const float x = lds[p * PP + j * PT + t + T * m];
+          if (part) z[m * T + j].y = x;
+          else z[m * T + j].x = x;
+        }
+      if (part == 0 || more) __syncthreads();
+    }
+  };
+  swap(v, true);
+  swap(u, false);
+  const int k1 = k0 + p;
+  if (k1 > n1 / 2) return;
+  const int64_t N = (int64_t)1 << a.log_n;
+  float2* x = a.out + (int64_t)blockIdx.y * a.out_pitch;
+  const bool self = k1 == 0 || k1 == n1 / 2;              // rows that are their own mirror
+#pragma unroll
+  for (int m = 0; m < NB; ++m) {
+    dft_two<T, false>(v + m * T);
+    dft_two<T, false>(u + m * T);
+    const int64_t f0 = k1 + ((int64_t)(t + T * m) << log_a);
+#pragma unroll
+    for (int j = 0; j < T; ++j) {
+      const int64_t f = f0 + ((int64_t)(E * j) << log_a);
+      const float2 zf = v[m * T + j], zc = u[m * T + j];
+      const float2 av = make_float2(0.5f * (zf.x + zc.x), 0.5f * (zf.y + zc.y));
+      const float2 d = make_float2(0.5f * (zf.x - zc.x), 0.5f * (zf.y - zc.y));
+      const float2 w = turn_phasor<false>((uint32_t)f << (31 - a.log_n));        // exp(-2 pi i f / L)
+      const float2 wb = cmulf(w, make_float2(d.y, -d.x));                        // w (-i d)
+      x[f] = make_float2(av.x + wb.x, av.y + wb.y);
+      if (!self || f == 0) x[N - f] = make_float2(av.x - wb.x, wb.y - av.y);
+    }
+  }
+}
+
 namespace {
 constexpr int kLongLogR = 4;
 
-template <bool INV, int MODE>
+template <bool LAST>
 hipError_t launch_pass(int logr, LongPassArgs a, hipStream_t st) {
   const int64_t nb = (int64_t)1 << (a.log_n - logr);
   const dim3 grid((unsigned)((nb + 255) / 256), (unsigned)a.n_series);
   switch (logr) {
-    case 1: hipLaunchKernelGGL((k_fft_pass<1, INV, MODE>), grid, dim3(256), 0, st, a); break;
-    case 2: hipLaunchKernelGGL((k_fft_pass<2, INV, MODE>), grid, dim3(256), 0, st, a); break;
-    case 3: hipLaunchKernelGGL((k_fft_pass<3, INV, MODE>), grid, dim3(256), 0, st, a); break;
-    case 4: hipLaunchKernelGGL((k_fft_pass<4, INV, MODE>), grid, dim3(256), 0, st, a); break;
-    case 5: hipLaunchKernelGGL((k_fft_pass<5, INV, MODE>), grid, dim3(256), 0, st, a); break;
+    case 1: hipLaunchKernelGGL((k_c2r_pass<1, LAST>), grid, dim3(256), 0, st, a); break;
+    case 2: hipLaunchKernelGGL((k_c2r_pass<2, LAST>), grid, dim3(256), 0, st, a); break;
+    case 3: hipLaunchKernelGGL((k_c2r_pass<3, LAST>), grid, dim3(256), 0, st, a); break;
+    case 4: hipLaunchKernelGGL((k_c2r_pass<4, LAST>), grid, dim3(256), 0, st, a); break;
+    case 5: hipLaunchKernelGGL((k_c2r_pass<5, LAST>), grid, dim3(256), 0, st, a); break;
     default: return hipErrorInvalidValue;
   }
   return hipGetLastError();
@@ -489,9 +628,23 @@ void pass_radices(int log_n, int* logr, int* n) {
     left -= r;
   }
 }
+
+template <int LOGA>
+void launch_long_cols(const LongPassArgs& a, hipStream_t st) {
+  const dim3 grid((unsigned)(1 << (a.log_n - LOGA - 4)), (unsigned)a.n_series), block(kLongCols * LongShape<LOGA>::T);
+  if (a.in_u8 != nullptr) hipLaunchKernelGGL((k_long_cols<LOGA, true>), grid, block, 0, st, a);
+  else hipLaunchKernelGGL((k_long_cols<LOGA, false>), grid, block, 0, st, a);
+}
+
+template <int LOGB>
+void launch_long_rows(const LongPassArgs& a, hipStream_t st) {
+  const int n_tile = (1 << (a.log_n - LOGB)) / 2 / kLongPairs + 1;   // pairs 0 .. N1 / 2
+  hipLaunchKernelGGL((k_long_rows<LOGB>), dim3((unsigned)((n_tile + 7) / 8 * 8), (unsigned)a.n_series),
+                     dim3(kLongPairs * LongShape<LOGB>::T), 0, st, a, n_tile);
+}
 }  // namespace
 
-// Forward real transform of every (row, chunk) series of length L = 2^(log_n + 1) into
+// Forward real transform of every (row, chunk) series of length L = 2^(log_n + 1) (2^17 .. 2^22) into
 // X [series][pitch] (bins 0 .. N); `work` holds one series-sized complex buffer per series.
 hipError_t launch_r2c_long(const FftArgs& f, float2* work, float* l1sum, hipStream_t st) {
   LongPassArgs a;
@@ -502,45 +655,39 @@ hipError_t launch_r2c_long(const FftArgs& f, float2* work, float* l1sum, hipStre
   a.n_samp = f.n_samp;
   a.in_u8 = f.in_u8;
   a.in_f32 = f.in_f32;
-  int logr[16], np = 0;
-  pass_radices(a.log_n, logr, &np);
-  // ping-pong: the last pass must land in `work` so the split can write X
-  float2* bufs[2] = {work, f.X};
-  int cur = (np % 2 == 1) ? 0 : 1;          // buffer receiving pass 0's output
-  hipError_t e = hipSuccess;
   if (f.l1max != nullptr) {
     hipLaunchKernelGGL(k_zero_f32, dim3((unsigned)((a.n_series + 255) / 256)), dim3(256), 0, st, l1sum,
                        (int64_t)a.n_series);
     a.l1sum = l1sum;
   }
-  int log_ns = 0;
-  for (int p = 0; p < np; ++p) {
-    a.log_ns = log_ns;
-    a.out = bufs[cur];
-    a.out_pitch = cur == 0 ? ((int64_t)1 << a.log_n) : f.pitch;
-    if (p == 0) {
-      e = f.in_u8 != nullptr ? launch_pass<false, kPassLoadU8>(logr[p], a, st)
-                             : launch_pass<false, kPassLoadF32>(logr[p], a, st);
-      a.l1sum = nullptr;
-    } else {
-      e = launch_pass<false, kPassComplex>(logr[p], a, st);
-    }
-    if (e != hipSuccess) return e;
-    a.in = bufs[cur];
-    a.in_pitch = a.out_pitch;
-    cur ^= 1;
-    log_ns += logr[p];
+  // N1 = 2^(log_n - log_b) rows of N2 = 2^log_b columns: about equal, the rows at most 2^10 points long
+  // (a thread holds two of them)
+  const int log_b = a.log_n / 2 < 10 ? a.log_n / 2 : 10;
+  if (log_b < 8) return hipErrorInvalidValue;
+  a.out = work;
+  a.out_pitch = (int64_t)1 << a.log_n;
+  switch (a.log_n - log_b) {
+    case 8: launch_long_cols<8>(a, st); break;
+    case 9: launch_long_cols<9>(a, st); break;
+    case 10: launch_long_cols<10>(a, st); break;
+    case 11: launch_long_cols<11>(a, st); break;
+    default: return hipErrorInvalidValue;
   }
-  if (f.l1max != nullptr)
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  if (f.l1max != nullptr) {
     hipLaunchKernelGGL(k_l1_max, dim3((unsigned)((f.n_chunks + 63) / 64)), dim3(64), 0, st, l1sum, f.n_rows,
                        f.n_chunks, f.l1max);
-  // final result is in work (pitch N); split into X
+  }
   a.in = work;
-  a.in_pitch = (int64_t)1 << a.log_n;
+  a.in_pitch = a.out_pitch;
   a.out = f.X;
   a.out_pitch = f.pitch;
-  const int64_t nbins = ((int64_t)1 << a.log_n) + 1;
-  hipLaunchKernelGGL(k_r2c_split, dim3((unsigned)((nbins + 255) / 256), (unsigned)a.n_series), dim3(256), 0, st, a);
+  switch (log_b) {
+    case 8: launch_long_rows<8>(a, st); break;
+    case 9: launch_long_rows<9>(a, st); break;
+    default: launch_long_rows<10>(a, st); break;
+  }
   return hipGetLastError();
 }
 
@@ -576,8 +723,7 @@ hipError_t launch_c2r_long(const FftArgs& f, float2* work, float2* work2, hipStr
     a.in_pitch = N;
     a.out = bufs[cur ^ 1];
     a.out_pitch = N;
-    e = (p == np - 1) ? launch_pass<true, kPassStoreReal>(logr[p], a, st)
-                      : launch_pass<true, kPassComplex>(logr[p], a, st);
+    e = p == np - 1 ? launch_pass<true>(logr[p], a, st) : launch_pass<false>(logr[p], a, st);
     if (e != hipSuccess) return e;
     cur ^= 1;
     log_ns += logr[p];

@@ -100,49 +100,6 @@ __device__ __forceinline__ void grid_barrier() {
   __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
 }
 
-// u, t -> u + w t, u - w t with the second as 2 u - (u + w t): 6 fused operations.
-__device__ __forceinline__ void bfly(float2& u, float2& t, float wr, float wi) {
-  const float ar = fmaf(-wi, t.y, fmaf(wr, t.x, u.x));
-  const float ai = fmaf(wi, t.x, fmaf(wr, t.y, u.y));
-  t = make_float2(fmaf(2.0f, u.x, -ar), fmaf(2.0f, u.y, -ai));
-  u = make_float2(ar, ai);
-}
-
-// Stages LOGB .. LOG2(R) of a decimation-in-time transform with sign +, in place on x (bit-reversed
-// order in, natural order out): stage s joins blocks of 2^(s-1).
-template <int R, int LOGB>
-__device__ __forceinline__ void dit_stages(float2* x) {
-  constexpr RootTable<R, true> tab{};
-#pragma unroll
-  for (int half = 1 << (LOGB - 1); half < R; half *= 2) {
-#pragma unroll
-    for (int s = 0; s < R; s += 2 * half) {
-#pragma unroll
-      for (int j = 0; j < half; ++j) {
-        float2& u = x[s + j];
-        float2& t = x[s + j + half];
-        const int m = j * (R / (2 * half));          // exp(2 pi i m / R)
-        if (m == 0) {
-          const float2 d = f2sub(u, t);
-          u = f2add(u, t);
-          t = d;
-        } else if (4 * m == R) {                     // i t
-          const float2 p = make_float2(u.x - t.y, u.y + t.x);
-          t = make_float2(u.x + t.y, u.y - t.x);
-          u = p;
-        } else if (2 * half == R) {                  // last stage: outputs that nobody reads drop out one by one
-          const float c = tab.c[m], sn = tab.s[m];
-          const float2 p = make_float2(fmaf(-sn, t.y, fmaf(c, t.x, u.x)), fmaf(sn, t.x, fmaf(c, t.y, u.y)));
-          t = make_float2(fmaf(sn, t.y, fmaf(-c, t.x, u.x)), fmaf(-sn, t.x, fmaf(-c, t.y, u.y)));
-          u = p;
-        } else {
-          bfly(u, t, tab.c[m], tab.s[m]);
-        }
-      }
-    }
-  }
-}
-
 // The grid point, counted on through the turns, of the first tap of a channel with `inc` turns per
 // bin and trial, at bin f (M points later, so that it is not negative).
 template <int LOGM>
@@ -638,7 +595,7 @@ __global__ __launch_bounds__(64 * grid_bins<POWER>(), 1) void k_phasor_grid(Grid
           }
         }
       }
-      dit_stages<64, 1>(v);
+      dit_stages<64, 1, true>(v);
       wave_order();
 #pragma unroll
       for (int k1 = 0; k1 < 64; ++k1) reg[lane * XP + k1] = v[k1];
@@ -663,7 +620,7 @@ __global__ __launch_bounds__(64 * grid_bins<POWER>(), 1) void k_phasor_grid(Grid
           const float2 w1 = twiddle(l1);
           bfly(x[q], x[q + 1], w1.x, w1.y);
         }
-        dit_stages<LM, 2>(x);
+        dit_stages<LM, 2, true>(x);
         if (c0 != 0) {                               // the grid begins c0 points (64 at a time) into the circle
           const float2 rot = turn_phasor<true>((uint32_t)((c0 >> 6) * lane) << (32 - (LOGM - 6)));
 #pragma unroll
