@@ -40,11 +40,11 @@ namespace {
 constexpr size_t kAlign = 256;
 size_t align_up(size_t v) { return (v + kAlign - 1) / kAlign * kAlign; }
 
-enum Kind { kValu = 0, kMfmaF32 = 1, kSplitF16 = 2, kSplitBf16 = 3, kFac = 4, kGrid = 5 };
+enum Kind { kValu = 0, kMfmaF32 = 1, kSplitF16 = 2, kSplitBf16 = 3, kFac = 4, kGrid = 5, kFew = 6 };
 
 struct Choice {
   int kind = kValu;
-  int variant = 0;       // matrix-core tile variant, chunks per thread of the VALU kernel, or the
+  int variant = 0;       // matrix-core tile variant, chunks per thread of the VALU kernels, or the
                          // precision of a DM-factorised kernel
   bool persist = false;
   std::string name() const {
@@ -56,6 +56,7 @@ struct Choice {
       case kFac: std::snprintf(buf, sizeof buf, "fac_%s/%s", variant == FDD_FP32 ? "f32" : variant == FDD_FP16_SPLIT ? "f16_split" : "bf16_split",
                                persist ? "persistent" : "grid"); break;
       case kGrid: std::snprintf(buf, sizeof buf, "grid"); break;
+      case kFew: std::snprintf(buf, sizeof buf, "fac_few/nk%d", variant); break;
       default: std::snprintf(buf, sizeof buf, "valu/nk%d", variant); break;
     }
     return buf;
@@ -206,15 +207,16 @@ const Choice& chosen(const fdd_batch_s* b, const Launch& l) {
 }
 
 // Candidate kernels of the phasor sum for a plan's precision and chunk count; `fac` adds the
-// DM-factorised kernels (uniform DM grid, exact delays).  cands[0] is what fdd_execute runs.
-Class make_class(const fdd_plan_s* p, int N, bool fac, bool fac_default) {
+// DM-factorised kernels (uniform DM grid, exact delays), `few` the vector kernel on their tables.
+// cands[0] is what fdd_execute runs.
+Class make_class(const fdd_plan_s* p, int N, bool fac, bool fac_default, bool few) {
   Class c;
   // the direct matrix-core kernels run over chunk groups of at most kDirectMaxChunks
   const int NG = chunk_group_max(N);
   c.nt = (2 * NG + 15) / 16;
   char key[112];
   const int prec = p->desc.precision;
-  const char* fs = fac_default ? "+fac0" : fac ? "+fac" : "";
+  const char* fs = few ? "+fac0few" : fac_default ? "+fac0" : fac ? "+fac" : "";
   if (prec == FDD_FP16_SPLIT || prec == FDD_BF16_SPLIT) {
     const int kind = prec == FDD_FP16_SPLIT ? kSplitF16 : kSplitBf16;
     std::snprintf(key, sizeof key, "%s/L%lld/nt%d%s", kind == kSplitF16 ? "f16split" : "bf16split",
@@ -239,6 +241,7 @@ Class make_class(const fdd_plan_s* p, int N, bool fac, bool fac_default) {
     if (fac_default) c.cands.insert(c.cands.begin(), g);
     else c.cands.push_back(g);
     c.cands.push_back(q);
+    if (few) c.cands.insert(c.cands.begin(), {kFew, N == 1 ? 1 : 4, false});
   }
   c.key = key;
   c.ms.assign(c.cands.size(), -1.0f);
@@ -350,12 +353,12 @@ fdd_status fill(fdd_batch_s* b, const void* const* in, float* const* out) {
         a.log_len = p->log_len;
         const Choice& ch = chosen(b, l);
         a.tile_variant = ch.kind == kMfmaF32 ? ch.variant : 0;
-        if (ch.kind == kFac) {
+        if (ch.kind == kFac || ch.kind == kFew) {
           a.ptab = (const uint4*)(b->d_tab + sk.ftab);
           a.vtab = a.ptab + (size_t)d.n_chan * (size_t)sk.coarse;
           a.n_coarse = sk.coarse;
           a.n_fine = sk.fine;
-          tiles = phasor_fac_tiles(&a, d.precision);
+          tiles = ch.kind == kFac ? phasor_fac_tiles(&a, d.precision) : phasor_valu_tiles(&a, ch.variant);
         } else if (ch.kind == kValu) {
           tiles = phasor_valu_tiles(&a, ch.variant);
         } else {
@@ -467,7 +470,7 @@ hipError_t enqueue_launch(fdd_batch_s* b, const Launch& l, const void* const* in
         case kSplitF16: return launch_phasor_split_grouped(false, nt, ch.persist, g, st);
         case kSplitBf16: return launch_phasor_split_grouped(true, nt, ch.persist, g, st);
         case kFac: return launch_phasor_fac_grouped(ch.variant, ch.persist, g, st);
-        default: return launch_phasor_valu_grouped(ch.variant, g, st);
+        default: return launch_phasor_valu_grouped(ch.variant, ch.kind == kFew, g, st);
       }
     }
   }
@@ -642,10 +645,11 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
     // the kernel fdd_execute would pick: its own choice for a lone beam, the same rule for a stack
     const bool fac_default =
         sk.beams.size() == 1 ? p->fac_fine > 0 && p->facw_nt == 0 : (sk.fine > 0 && sk.n_chunks <= 2);
+    const bool few = fac_default && p->fac_few && fac_few_pays(p, sk.n_chunks);
     // the grid form where fdd_execute takes it (a stack by the same rule for its own chunk count)
     if (!p->grid.empty()) (void)grid_runs(p, sk.n_chunks, &sk.grid);
     if (!sk.grid.empty()) sk.fine = sk.coarse = 0;
-    Class c = sk.grid.empty() ? make_class(p, sk.n_chunks, sk.fine > 0, fac_default) : grid_class(p);
+    Class c = sk.grid.empty() ? make_class(p, sk.n_chunks, sk.fine > 0, fac_default, few) : grid_class(p);
     auto it = class_of.find(c.key);
     if (it == class_of.end()) {
       std::string name;

@@ -133,6 +133,11 @@ hipError_t launch_grid_run(fdd_plan_t p, const GridRun& r, const PhasorArgs& all
   return launch_phasor_grid(a, st);
 }
 
+// The DM-factorised phasor sum of a plan of one or two chunks.
+hipError_t launch_fac(fdd_plan_t p, const PhasorArgs& a, hipStream_t st) {
+  return p->fac_few ? launch_phasor_valu(a, st) : launch_phasor_fac(a, p->desc.precision, st);
+}
+
 // The direct matrix-core phasor sums (Eq. 7 batched over the overlap-save chunks), one launch
 // per chunk group.
 hipError_t launch_direct(fdd_plan_t p, const PhasorArgs& a, hipStream_t st) {
@@ -226,7 +231,7 @@ namespace {
 fdd_status execute_body(fdd_plan_t p, const void* in, float* out, hipStream_t st) {
   fdd_status s;
   mark(p, 0, st);
-  s = forward(p, in, p->desc.precision != FDD_FP32 && !uses_grid(p), st);
+  s = forward(p, in, p->desc.precision != FDD_FP32 && !uses_grid(p) && !p->fac_few, st);
   if (s != FDD_OK) return s;
   PhasorArgs all = phasor_args(p);
   all.Yr = (float*)(p->d_ws + p->ws.Yr);
@@ -242,7 +247,7 @@ fdd_status execute_body(fdd_plan_t p, const void* in, float* out, hipStream_t st
     if (uses_grid(p)) break;
     const PhasorArgs a = segment_args(p, all, sg, false);
     if (p->facw_nt > 0) e = launch_phasor_facw(a, p->desc.precision, p->facw_nt, st);
-    else if (p->fac_fine > 0) e = launch_phasor_fac(a, p->desc.precision, st);
+    else if (p->fac_fine > 0) e = launch_fac(p, a, st);
     else if (p->kernel == "mfma_f32" || p->kernel == "mfma_f16_split" || p->kernel == "mfma_bf16_split")
       e = launch_direct(p, a, st);
     else e = launch_phasor_valu(a, st);
@@ -323,7 +328,7 @@ fdd_status fdd_power_spectrum(fdd_plan_t p, const void* in, float* out, void* st
   if (!p->desc.single_chunk) return fail(FDD_E_UNSUPPORTED, "power spectra need a single-chunk plan");
   hipStream_t st = (hipStream_t)stream;
   mark(p, 0, st);
-  s = forward(p, in, p->desc.precision != FDD_FP32 && !uses_grid(p), st);
+  s = forward(p, in, p->desc.precision != FDD_FP32 && !uses_grid(p) && !p->fac_few, st);
   if (s != FDD_OK) return s;
   PhasorArgs all = phasor_args(p);
   all.P = out;
@@ -340,7 +345,7 @@ fdd_status fdd_power_spectrum(fdd_plan_t p, const void* in, float* out, void* st
   for (const Segment& sg : p->segs) {
     if (uses_grid(p)) break;
     const PhasorArgs a = segment_args(p, all, sg, true);
-    if (p->fac_fine > 0) e = launch_phasor_fac(a, p->desc.precision, st);
+    if (p->fac_fine > 0) e = launch_fac(p, a, st);
     else if (p->kernel == "mfma_f16_split") e = launch_phasor_split(a, false, st);
     else if (p->kernel == "mfma_bf16_split") e = launch_phasor_split(a, true, st);
     else e = launch_phasor_valu(a, st);
@@ -375,7 +380,7 @@ fdd_status fdd_power_spectrum_scaled(fdd_plan_t p, const void* in, float* out, v
       PhasorArgs a = segment_args(p, all, sg, true);
       a.n_bins = p->sc_fmin;
       hipError_t e;
-      if (p->fac_fine > 0) e = launch_phasor_fac(a, prec, st);
+      if (p->fac_fine > 0) e = launch_fac(p, a, st);
       else if (p->kernel == "mfma_f16_split") e = launch_phasor_split(a, false, st);
       else if (p->kernel == "mfma_bf16_split") e = launch_phasor_split(a, true, st);
       else e = launch_phasor_valu(a, st);

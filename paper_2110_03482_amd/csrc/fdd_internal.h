@@ -368,7 +368,7 @@ int64_t phasor_split_tiles(PhasorArgs* a);
 hipError_t launch_phasor_split_grouped(bool bf16, int nt, bool persist, const Group<PhasorArgs>& g,
                                        hipStream_t st);
 int64_t phasor_valu_tiles(PhasorArgs* a, int nk);
-hipError_t launch_phasor_valu_grouped(int nk, const Group<PhasorArgs>& g, hipStream_t st);
+hipError_t launch_phasor_valu_grouped(int nk, bool fac, const Group<PhasorArgs>& g, hipStream_t st);
 constexpr int kMfmaF32Variants = 5;
 
 // Byte offsets of the workspace regions (256-byte aligned).
@@ -428,6 +428,7 @@ struct fdd_plan_s {
   bool ws_owned = false;
   bool dry_run = false;
   std::string kernel = "valu";
+  bool fac_few = false;                // the factorised tables feed the vector kernel: few trials
   int tile_variant = 0;                 // FDD_TILE_VARIANT override
   // DM factorisation (uniform DM grid, exact delays): trial j = a * fac_fine + b
   int fac_fine = 0, fac_coarse = 0;     // 0: not factorised
@@ -471,6 +472,7 @@ void factor_tables(const fdd_plan_s* p, int fine, int coarse, double dm0, double
 void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out);
 // The plan's trials as grid runs for n_chunks chunks; false if they have no such form or the kernel
 // family of the plan is the faster one.
+bool fac_few_pays(const fdd_plan_s* p, int64_t n_chunks);
 bool grid_runs(const fdd_plan_s* p, int n_chunks, std::vector<GridRun>* out);
 size_t grid_scratch_bytes(const fdd_plan_s* p, const GridRun& r);
 // Channels by ascending delay.

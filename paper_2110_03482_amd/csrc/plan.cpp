@@ -214,10 +214,10 @@ static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& ru
   int dm_tile = 64, min_chan = 64, col_tile = 8;
   if (p->facw_nt > 0) {
     rate = 240.0, dm_tile = 128, min_chan = 96, col_tile = 1;
+  } else if (p->fac_few || p->kernel == "valu") {
+    rate = 22.0, dm_tile = 4, min_chan = 1, col_tile = 1;
   } else if (fac) {
     rate = fp32 ? 92.0 : 170.0, dm_tile = 2048, min_chan = 1, col_tile = 1;
-  } else if (p->kernel == "valu") {
-    rate = 8.0, dm_tile = 1, min_chan = 1, col_tile = 1;
   }
   const auto up = [](int n, int to) { return (double)((n + to - 1) / to * to); };
   for (const GridRun& r : runs) {
@@ -233,6 +233,15 @@ static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& ru
     direct += 6.0 + 8.0 * up(r.n, dm_tile) * (double)std::max(n_chan, min_chan) * bins * up(N, col_tile) / (rate * 1e6);
   }
   return grid < direct;
+}
+
+// Few trials leave most of the 64 coarse rows of a workgroup of the factorised kernels idle (their
+// time hardly depends on n_dm up to 1024), and the vector kernel, whose time does, is faster.  The
+// lines lie below where both are equal, e.g. 64 channels, one chunk of 65536: 256 trials 191 us
+// against 354 (FP32) and 202 (split), 512 trials 359 against 359 and 212; two chunks, 128 trials: 193
+// against 361 and 204.
+bool fac_few_pays(const fdd_plan_s* p, int64_t n_chunks) {
+  return (int64_t)p->desc.n_dm * n_chunks <= (p->desc.precision == FDD_FP32 ? 384 : 160);
 }
 
 // Scratch of one run's launches.
@@ -363,7 +372,7 @@ static void build_host_tables(fdd_plan_s* p) {
     keep(sg.tw, tw.data(), tw.size() * sizeof(float2));
   }
   std::vector<uint4> tab;
-  if (!p->grid.empty() && !p->scaled) {
+  if (!p->grid.empty()) {
     // no phase table
   } else if (p->fac_fine > 0) {
     factor_tables(p, p->fac_fine, p->fac_coarse, p->fac_dm0, p->fac_step, &tab);
@@ -457,15 +466,13 @@ static fdd_status layout(fdd_plan_s* p) {
   if (!mul_ok((size_t)d.n_chan * rows_tab, sizeof(uint4), &w.ptab_bytes))
     return fail(FDD_E_NOMEM, "phase table size overflows");
   if (!p->grid.empty()) {
-    // the grid kernel reads no phase table: its schedules take that space, unless the plan's
-    // scaled-DM spectra need the table for their lowest bins
+    // the grid kernel reads no phase table: its schedules take that space
     w.sched_bytes = 0;
     for (const GridRun& r : p->grid) w.sched_bytes = std::max(w.sched_bytes, grid_scratch_bytes(p, r));
-    if (!p->scaled) w.ptab_bytes = std::max(w.ptab_bytes, w.sched_bytes);
+    w.ptab_bytes = std::max(w.ptab_bytes, w.sched_bytes);
   }
   put(&w.ptab, w.ptab_bytes);
   w.sched = w.ptab;
-  if (!p->grid.empty() && p->scaled) put(&w.sched, w.sched_bytes);
   w.scale_bytes = (size_t)p->n_chunks * sizeof(float);
   put(&w.scale, w.scale_bytes);
   if (d.input == FDD_IN_U8_TIME_MAJOR) {
@@ -733,6 +740,7 @@ fdd_status fdd_plan(const fdd_plan_desc* desc, fdd_plan_t* out) {
       p->fac_dm0 = dm0;
       p->fac_step = step;
       p->kernel = d.precision == FDD_FP32 ? "fac_f32" : d.precision == FDD_FP16_SPLIT ? "fac_f16_split" : "fac_bf16_split";
+      p->fac_few = fe == nullptr && fac_few_pays(p, p->n_chunks);   // a family asked for by name keeps its own kernel
     }
     // Overlap-save plans: the chunked factorised kernels, in which every coarse phasor serves
     // 2 B N matrix-core columns instead of the direct kernels' 2 N.  They need the inverse's
@@ -779,10 +787,12 @@ fdd_status fdd_plan(const fdd_plan_desc* desc, fdd_plan_t* out) {
     }
   }
   // The grid form of the phasor sum (FDD_GRID=0: never, 1: wherever it applies).  A kernel family
-  // asked for by name keeps its own kernels.
+  // asked for by name keeps its own kernels, and so does a plan for scaled DMs, whose low bins are
+  // those of its power spectra to the last bit.
   {
     const char* ge = std::getenv("FDD_GRID");
-    const bool off = (ge != nullptr && std::strcmp(ge, "0") == 0) || std::getenv("FDD_FACTOR") != nullptr ||
+    const bool off = (ge != nullptr && std::strcmp(ge, "0") == 0) || (d.flags & FDD_PLAN_SCALED_DM) != 0 ||
+                     std::getenv("FDD_FACTOR") != nullptr ||
                      std::getenv("FDD_TILE_VARIANT") != nullptr || std::getenv("FDD_PHASE_TABLE") != nullptr;
     p->grid_force = ge != nullptr && std::strcmp(ge, "1") == 0;
     if (!off) (void)grid_runs(p, (int)p->n_chunks, &p->grid);
