@@ -10,16 +10,16 @@
 // A workgroup owns 4 DMs and 64 FV bins, and its 4 waves share the channels; at the end wave i
 // collects DM i through LDS.  Lanes hold neighbouring bins, so X is read and Y written in whole
 // lines, and each value read serves 4 DMs.  Per channel and DM a lane evaluates the phasor of its
-// first bin and that of 64 bins on from the exact 64-bit increment and walks 8 bins by complex
-// multiplication (at most 7 steps, so the recurrence error stays at a few float32 ulps), then
-// evaluates again.  Small problems take fewer bins per lane and more workgroups, with the same steps
-// to every bin: a result does not depend on FV.
+// first bin from the exact 64-bit increment and multiplies it by those of 64, 128 .. 448 bins, which 8
+// lanes evaluate for all; past 8 bins it evaluates again.  Small problems take fewer bins per lane and
+// more workgroups, with the same steps to every bin: a result does not depend on FV.
 // Bound: instruction issue, 8 operations per channel, bin and DM, and 4 or more for the
 // phasors.
-//   128 channels, 2048 DMs, one chunk of 65536 samples, rounded delays:   24.4 -> 2.9 ms (it
+//   128 channels, 2048 DMs, one chunk of 65536 samples, rounded delays:  24.4 -> 3.4 ms (it
 //   was one DM per thread with 16 neighbouring bins, 128 bytes apart between lanes);
 //   64 channels, 64 equally spaced DMs, one chunk of 4096 samples:  39.2 (64 rows of 32 DMs on the
-//   matrix cores, of which 2 were in use) -> 15.1 us.
+//   matrix cores, of which 2 were in use) -> 22 us; reading the next
+//   channel ahead changes nothing.
 //
 // With P set, the epilogue writes power spectra |Y|^2 for bins below L/2 (Sec. 5) instead of
 // the complex result.
@@ -49,17 +49,15 @@ __device__ __forceinline__ void phasor_valu_body(const PhasorArgs& a, const int 
   const int dm0 = by * kDms;
   const int k0 = bz * NK;
   float2 acc[kDms][NK][FV];
-  int ia[kDms], ib[kDms];                             // table columns
 #pragma unroll
-  for (int d = 0; d < kDms; ++d) {
-    const int dm = min(dm0 + d, a.n_dm - 1);          // a clamped DM's results are not stored
-    ia[d] = FAC ? dm / a.n_fine : dm;
-    ib[d] = FAC ? dm % a.n_fine : 0;
+  for (int d = 0; d < kDms; ++d)
 #pragma unroll
     for (int k = 0; k < NK; ++k)
 #pragma unroll
       for (int i = 0; i < FV; ++i) acc[d][k][i] = make_float2(0.0f, 0.0f);
-  }
+  // table columns of this lane's DM (a clamped one's results are not stored)
+  const int own = min(dm0 + lane / kSeed % kDms, a.n_dm - 1);
+  const int ia = FAC ? own / a.n_fine : own, ib = FAC ? own % a.n_fine : 0;
   const int r0 = bx * FV % kSeed;
   const int na = FAC ? a.n_coarse : a.n_dm;
   int at[FV];
@@ -74,30 +72,37 @@ __device__ __forceinline__ void phasor_valu_body(const PhasorArgs& a, const int 
 #pragma unroll
       for (int i = 0; i < FV; ++i) x[k][i] = xk[at[i]];
     }
-#pragma unroll
-    for (int d = 0; d < kDms; ++d) {
-      const uint4 e = a.ptab[(int64_t)c * na + ia[d]];
-      uint64_t inc = ((uint64_t)e.y << 32) | e.x;
+    // lane 8 d + i has the increment of DM d and the phasor of 64 i bins
+    uint64_t inc;
+    {
+      const uint4 e = a.ptab[(int64_t)c * na + ia];
+      inc = ((uint64_t)e.y << 32) | e.x;
       if constexpr (FAC) {
-        const uint4 v = a.vtab[(int64_t)c * a.n_fine + ib[d]];
+        const uint4 v = a.vtab[(int64_t)c * a.n_fine + ib];
         inc += ((uint64_t)v.y << 32) | v.x;
       }
-      const PhaseInc pi = {(uint32_t)(inc >> 32), (uint32_t)inc};
-      float2 w, step;
-      sincos_turn(phase_at(pi, 64u), &step.y, &step.x);
-      if constexpr (FV < kSeed) {
-        sincos_turn(phase_at(pi, (uint32_t)(f0 - 64 * r0)), &w.y, &w.x);
-        for (int i = 0; i < r0; ++i) w = cmul(w, step);
-      }
+    }
+    const int hi = (int)(inc >> 32), lo = (int)(uint32_t)inc;
+    float2 far;
+    sincos_turn(phase_at(PhaseInc{(uint32_t)hi, (uint32_t)lo}, 64u * (uint32_t)(lane % kSeed)), &far.y, &far.x);
+#pragma unroll
+    for (int d = 0; d < kDms; ++d) {
+      const PhaseInc pi = {(uint32_t)__builtin_amdgcn_readlane(hi, kSeed * d), (uint32_t)__builtin_amdgcn_readlane(lo, kSeed * d)};
+      float2 w0;
 #pragma unroll
       for (int i = 0; i < FV; ++i) {
-        if (FV >= kSeed && i % kSeed == 0) sincos_turn(phase_at(pi, (uint32_t)(f0 + 64 * i)), &w.y, &w.x);
+        if (i % kSeed == 0) sincos_turn(phase_at(pi, (uint32_t)(f0 - 64 * r0 + 64 * i)), &w0.y, &w0.x);
+        float2 w = w0;
+        if (FV < kSeed || i % kSeed != 0) {
+          const int from = kSeed * d + r0 + i % kSeed;
+          w = cmul(w0, make_float2(__int_as_float(__builtin_amdgcn_readlane(__float_as_int(far.x), from)),
+                                   __int_as_float(__builtin_amdgcn_readlane(__float_as_int(far.y), from))));
+        }
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
           acc[d][k][i].x = fmaf(w.x, x[k][i].x, fmaf(-w.y, x[k][i].y, acc[d][k][i].x));
           acc[d][k][i].y = fmaf(w.x, x[k][i].y, fmaf(w.y, x[k][i].x, acc[d][k][i].y));
         }
-        if (i + 1 < FV && (i + 1) % kSeed != 0) w = cmul(w, step);
       }
     }
   }
@@ -158,14 +163,14 @@ __device__ __forceinline__ void phasor_valu_body(const PhasorArgs& a, const int 
 }
 
 template <int FV, int NK, bool FAC>
-__global__ __launch_bounds__(64 * kDms) void k_phasor_valu(PhasorArgs a) {
+__global__ __launch_bounds__(64 * kDms, 2) void k_phasor_valu(PhasorArgs a) {
   phasor_valu_body<FV, NK, FAC>(a, blockIdx.x, blockIdx.y, blockIdx.z);
 }
 
 // Batched form: tile t of beam b is block (t mod n_bb, (t / n_bb) mod n_dmt, t / (n_bb n_dmt))
 // of that beam's own launch.
 template <int FV, int NK, bool FAC>
-__global__ __launch_bounds__(64 * kDms) void k_phasor_valu_grouped(Group<PhasorArgs> g) {
+__global__ __launch_bounds__(64 * kDms, 2) void k_phasor_valu_grouped(Group<PhasorArgs> g) {
   const int t = blockIdx.y * gridDim.x + blockIdx.x;
   if (t >= g.total) return;
   const int b = group_beam(g.prefix, g.n_beams, t);

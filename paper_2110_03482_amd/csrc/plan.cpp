@@ -215,7 +215,7 @@ static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& ru
   if (p->facw_nt > 0) {
     rate = 240.0, dm_tile = 128, min_chan = 96, col_tile = 1;
   } else if (p->fac_few || p->kernel == "valu") {
-    rate = 22.0, dm_tile = 4, min_chan = 1, col_tile = 1;
+    rate = 20.0, dm_tile = 4, min_chan = 1, col_tile = 1;
   } else if (fac) {
     rate = fp32 ? 92.0 : 170.0, dm_tile = 2048, min_chan = 1, col_tile = 1;
   }
@@ -237,11 +237,12 @@ static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& ru
 
 // Few trials leave most of the 64 coarse rows of a workgroup of the factorised kernels idle (their
 // time hardly depends on n_dm up to 1024), and the vector kernel, whose time does, is faster.  The
-// lines lie below where both are equal, e.g. 64 channels, one chunk of 65536: 256 trials 191 us
-// against 354 (FP32) and 202 (split), 512 trials 359 against 359 and 212; two chunks, 128 trials: 193
-// against 361 and 204.
+// lines lie below where both are equal.  64 channels, one chunk of 4096: 256 trials 37 us against 40
+// (FP32); 64 trials 22.2 against 23.2 and 128 trials 31.6 against 24.3 (split).  65536: 256 trials 231
+// against 358 (FP32), 128 trials 134 against 202 (split); 16384, split, 128 trials: 54 against 62.
 bool fac_few_pays(const fdd_plan_s* p, int64_t n_chunks) {
-  return (int64_t)p->desc.n_dm * n_chunks <= (p->desc.precision == FDD_FP32 ? 384 : 160);
+  const int64_t most = p->desc.precision == FDD_FP32 ? 256 : p->L >= 16384 ? 128 : 64;
+  return (int64_t)p->desc.n_dm * n_chunks <= most;
 }
 
 // Scratch of one run's launches.

@@ -4,7 +4,7 @@ trials (increments from the coarse and fine tables) and with rounded delays (inc
 of the 4 waves, and power spectra.
 
 Tolerance 2e-6 of the row norm: the two transforms keep within 4e-7 each, the sum of up to 130 channels
-in four parts within 5e-7 and the 7 steps of the phasor recurrence within 5e-7.
+in four parts within 5e-7 and the product of two evaluated phasors within 2e-7.
 """
 import dataclasses
 
