@@ -100,6 +100,15 @@ __global__ void k_zero_u32(unsigned int* p, int n) {
   if (i < n) p[i] = 0u;
 }
 
+// Two samples at any place of a row (a chunk may begin at an odd sample): the compiler is told what
+// alignment there is, and gfx950 reads and writes them in one access all the same.
+struct __attribute__((packed, aligned(4))) SamplePair {
+  float a, b;
+};
+struct __attribute__((packed, aligned(1))) BytePair {
+  uint16_t w;
+};
+
 template <int LOGN, int LOGE, bool U8>
 __device__ __forceinline__ void r2c_body(const FftArgs& a, const int k, const int c) {
   using F = BlockFft<LOGN, LOGE, false>;
@@ -120,12 +129,12 @@ __device__ __forceinline__ void r2c_body(const FftArgs& a, const int k, const in
   float2 v[E];
   if constexpr (U8) {
     const uint8_t* src = in_u8 + (int64_t)c * n_samp + s0;
-    if (rem == (int)L && ((uintptr_t)src & 1u) == 0) {
-      // whole series, 2-byte aligned: one 16-bit load per point (x[2j] low byte, x[2j+1] high)
-      const uint16_t* s16 = reinterpret_cast<const uint16_t*>(src);
+    if (rem == (int)L) {
+      // whole series: one 16-bit load per point (x[2j] low byte, x[2j+1] high)
+      const BytePair* s16 = reinterpret_cast<const BytePair*>(src);
 #pragma unroll
       for (int q = 0; q < E; ++q) {
-        const uint32_t w = s16[t + T * q];
+        const uint32_t w = s16[t + T * q].w;
         v[q] = make_float2((float)(w & 0xffu) - zp, (float)(w >> 8) - zp);
       }
     } else {
@@ -138,10 +147,10 @@ __device__ __forceinline__ void r2c_body(const FftArgs& a, const int k, const in
     }
   } else {
     const float* src = in_f32 + (int64_t)c * n_samp + s0;
-    if (rem == (int)L && ((uintptr_t)src & 7u) == 0) {
-      const float2* s2 = reinterpret_cast<const float2*>(src);
+    if (rem == (int)L) {
+      const SamplePair* s2 = reinterpret_cast<const SamplePair*>(src);
 #pragma unroll
-      for (int q = 0; q < E; ++q) v[q] = s2[t + T * q];
+      for (int q = 0; q < E; ++q) v[q] = make_float2(s2[t + T * q].a, s2[t + T * q].b);
     } else {
 #pragma unroll
       for (int q = 0; q < E; ++q) {
@@ -271,18 +280,12 @@ __device__ __forceinline__ void c2r_body(const FftArgs& a, const int k, const in
   // Points q < qfull lie below lim for every thread (2 T (q + 1) <= lim); point qfull is cut
   // per sample; later points are all past it.  The tests on q are uniform.
   const int qfull = lim / (2 * T);
-  const bool al = ((uintptr_t)dst & 7u) == 0;
 #pragma unroll
   for (int q = 0; q < E; ++q) {
     const int s = 2 * (t + T * q);
     const float2 o = make_float2(v[q].x + add, v[q].y + add);
     if (q < qfull) {
-      if (al) {
-        *reinterpret_cast<float2*>(dst + s) = o;
-      } else {
-        dst[s] = o.x;
-        dst[s + 1] = o.y;
-      }
+      *reinterpret_cast<SamplePair*>(dst + s) = {o.x, o.y};
     } else if (q == qfull) {
       if (s < lim) dst[s] = o.x;
       if (s + 1 < lim) dst[s + 1] = o.y;
@@ -290,9 +293,154 @@ __device__ __forceinline__ void c2r_body(const FftArgs& a, const int k, const in
   }
 }
 
+// The inverse of 2^15 points (32 x 32 x 32), two columns t of Z[t + 1024 q] per thread: t = tid and
+// 1024 - tid, which hold the pairs Z[f], Z[N - f] that are made of the same Y[f], Y[N - f], so every
+// bin is read once and split once.  (tid = 0 has the columns 0 and 512, which pair with themselves;
+// 32 lanes prepare the second.)  With t = t0 + 32 t1 and m = r + 32 r1 + 1024 r2 the sums run over q,
+// t1 and t0, each in registers, with two exchanges through LDS, by halves of the threads' points so
+// that complex values fit and are moved whole.
+// Bound: one workgroup of 8 waves per CU (its points take half of the registers), so reading,
+// transforming and writing follow each other.  2048 x 21 series: 6.43 ms with 16-point butterflies,
+// three exchanges and every bin read twice, 5.4 to 5.7 ms so (20 GB, 4.2 ms at the rate of a copy).
+template <bool INTER>
+__device__ __forceinline__ void c2r_32k_body(const FftArgs& a, const int k, const int dm) {
+  constexpr int N = 1 << 15, Q = 32, C = 1024, P1 = 513;
+  constexpr int64_t L = 2 * (int64_t)N;
+  __shared__ float2 lds[Q * P1 + Q];
+  const int tid = (int)threadIdx.x;
+  const int row_chunks = a.row_chunks > 0 ? a.row_chunks : a.n_chunks;   // chunks per row of Y
+  const int64_t row = ((int64_t)dm * row_chunks + k) * a.pitch;
+  const float* __restrict__ yr = a.Yr + row;
+  const float* __restrict__ yi = a.Yi + row;
+  const float2* __restrict__ yc = a.Yc + row;
+  auto bin = [&](int f) {
+    if constexpr (INTER) return yc[f];
+    else return make_float2(yr[f], yi[f]);
+  };
+  const float scale = a.inv_n > 0.0f ? a.inv_n : 1.0f / (float)N;
+  const float hs = 0.5f * scale;
+  float2 u[2][Q];                                    // [column][q]
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    u[0][q] = bin(tid + C * q);
+    u[1][Q - 1 - q] = bin(N - tid - C * q);
+  }
+  // Z[f] and Z[N - f] (times scale) of Y[f], Y[N - f] and w = exp(2 pi i f / L)
+  auto split = [&](float2& yf, float2& ym, float2 w) {
+    const float2 s = make_float2(hs * (yf.x + ym.x), hs * (yf.y - ym.y));
+    const float2 d = make_float2(hs * (yf.x - ym.x), hs * (yf.y + ym.y));
+    const float2 b = cmulf(w, d);
+    yf = make_float2(s.x - b.y, s.y + b.x);
+    ym = make_float2(s.x + b.y, b.x - s.y);
+  };
+  if (tid < 64) {
+    const int q = tid & (Q - 1), f = C / 2 + C * q;
+    float2 yf = bin(f), ym = bin(N - f);
+    split(yf, ym, turn_phasor<true>((uint32_t)f << 16));
+    if (tid < Q) lds[Q * P1 + q] = yf;
+  }
+  if (tid == 0) u[0][0].y = u[1][Q - 1].y = 0.0f;    // bins 0 and N are real
+  {
+    const float2 w0 = turn_phasor<true>((uint32_t)tid << 16);
+    static_for<0, Q>([&](auto qi) {
+      constexpr int q = decltype(qi)::value;
+      split(u[0][q], u[1][Q - 1 - q], rotate_const<q, 2 * Q, true>(w0));
+    });
+  }
+  if (tid < 64) {
+    __builtin_amdgcn_fence(__ATOMIC_SEQ_CST, "wavefront", "local");
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const float2 z = lds[Q * P1 + q];
+      u[1][q] = tid == 0 ? z : u[1][q];
+    }
+  }
+  // over q, then exp(2 pi i t r / N); that of 1024 - tid from that of tid
+  dft_two<Q, true>(u[0]);
+  dft_two<Q, true>(u[1]);
+  float2 lo[8], hi;
+#pragma unroll
+  for (int i = 1; i < 8; ++i) lo[i] = turn_phasor<true>((uint32_t)(tid * i) << 17);
+  static_for<1, Q>([&](auto ri) {
+    constexpr int r = decltype(ri)::value;
+    if constexpr (r % 8 == 0) hi = turn_phasor<true>((uint32_t)(tid * r) << 17);
+    float2 w;
+    if constexpr (r < 8) w = lo[r];
+    else if constexpr (r % 8 == 0) w = hi;
+    else w = cmulf(hi, lo[r % 8]);
+    u[0][r] = cmulf(u[0][r], w);
+    const float2 m = rotate_const<r, Q, true>(make_float2(w.x, -w.y));
+    const float2 h = rotate_const<r, 2 * Q, true>(make_float2(1.0f, 0.0f));
+    u[1][r] = cmulf(u[1][r], tid == 0 ? h : m);
+  });
+  const int r = tid & (Q - 1), t0 = tid / Q;         // of the first set; the second has t0 + 16
+  float2 v[2][Q];
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    const int to = half == 0 ? tid : tid == 0 ? 0 : C / 2 - tid;
+    if (half == 1) __syncthreads();
+#pragma unroll
+    for (int i = 0; i < Q; ++i) lds[i * P1 + to] = u[half][i];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < Q / 2; ++i) v[s][half * (Q / 2) + i] = lds[r * P1 + t0 + s * (Q / 2) + Q * i];
+  }
+  // over t1, then exp(2 pi i t0 r1 / 1024)
+  dft_two<Q, true>(v[0]);
+  dft_two<Q, true>(v[1]);
+#pragma unroll
+  for (int i = 1; i < 8; ++i) lo[i] = turn_phasor<true>((uint32_t)(t0 * i) << 22);
+  static_for<1, Q>([&](auto ri) {
+    constexpr int r1 = decltype(ri)::value;
+    if constexpr (r1 % 8 == 0) hi = turn_phasor<true>((uint32_t)(t0 * r1) << 22);
+    float2 w;
+    if constexpr (r1 < 8) w = lo[r1];
+    else if constexpr (r1 % 8 == 0) w = hi;
+    else w = cmulf(hi, lo[r1 % 8]);
+    v[0][r1] = cmulf(v[0][r1], w);
+    v[1][r1] = cmulf(v[1][r1], rotate_const<r1, 2 * Q, true>(w));
+  });
+#pragma unroll
+  for (int half = 0; half < 2; ++half) {
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < Q; ++i) lds[t0 * C + Q * i + r] = v[half][i];
+    __syncthreads();
+#pragma unroll
+    for (int s = 0; s < 2; ++s)
+#pragma unroll
+      for (int i = 0; i < Q / 2; ++i) u[s][half * (Q / 2) + i] = lds[i * C + tid + s * (C / 2)];
+  }
+  dft_two<Q, true>(u[0]);
+  dft_two<Q, true>(u[1]);
+  const int64_t s0 = (int64_t)k * a.stride;
+  const bool full = a.full_chunks >= 0 ? k < a.full_chunks : s0 + L <= a.n_samp;
+  const float add = full ? a.add_full : 0.0f;
+  float* dst = a.out + (int64_t)dm * a.n_samp + s0;
+  const int lim = (int)((a.keep < a.n_samp - s0) ? a.keep : a.n_samp - s0);   // <= L
+  const int qfull = lim / (2 * C);                   // rows r2 below it are whole
+#pragma unroll
+  for (int r2 = 0; r2 < Q; ++r2) {
+#pragma unroll
+    for (int s = 0; s < 2; ++s) {
+      const int at = 2 * (tid + s * (C / 2) + C * r2);
+      const float2 o = make_float2(u[s][r2].x + add, u[s][r2].y + add);
+      if (r2 < qfull) {
+        *reinterpret_cast<SamplePair*>(dst + at) = {o.x, o.y};
+      } else if (r2 == qfull) {
+        if (at < lim) dst[at] = o.x;
+        if (at + 1 < lim) dst[at + 1] = o.y;
+      }
+    }
+  }
+}
+
 template <int LOGN, int LOGE, bool INTER>
 __global__ __launch_bounds__(1 << (LOGN - LOGE)) void k_c2r(FftArgs a) {
-  c2r_body<LOGN, LOGE, INTER>(a, blockIdx.x, blockIdx.y);
+  if constexpr (LOGN == 15) c2r_32k_body<INTER>(a, blockIdx.x, blockIdx.y);
+  else c2r_body<LOGN, LOGE, INTER>(a, blockIdx.x, blockIdx.y);
 }
 
 template <int LOGN, int LOGE, bool INTER>
@@ -303,7 +451,8 @@ __global__ __launch_bounds__(1 << (LOGN - LOGE)) void k_c2r_grouped(Group<FftArg
   const FftArgs a = g.beams[b];
   const int lid = bid - g.prefix[b];
   if (lid >= a.n_chunks * a.n_rows) return;
-  c2r_body<LOGN, LOGE, INTER>(a, lid % a.n_chunks, lid / a.n_chunks);
+  if constexpr (LOGN == 15) c2r_32k_body<INTER>(a, lid % a.n_chunks, lid / a.n_chunks);
+  else c2r_body<LOGN, LOGE, INTER>(a, lid % a.n_chunks, lid / a.n_chunks);
 }
 
 // ----------------------------------------------------------------------------- long transforms
@@ -456,10 +605,10 @@ __global__ __launch_bounds__((kLongCols * LongShape<LOGA>::T)) void k_long_cols(
   if constexpr (U8) {
     const float zp = full ? 128.0f : 0.0f;
     const uint8_t* src = a.in_u8 + (int64_t)row * a.n_samp + s0;
-    if (full && ((uintptr_t)src & 1u) == 0) {
+    if (full) {
 #pragma unroll
       for (int e = 0; e < E; ++e) {
-        const uint32_t w = reinterpret_cast<const uint16_t*>(src)[at + ((int64_t)(t + T * e) << log_b)];
+        const uint32_t w = reinterpret_cast<const BytePair*>(src)[at + ((int64_t)(t + T * e) << log_b)].w;
         v[e] = make_float2((float)(w & 0xffu) - zp, (float)(w >> 8) - zp);
       }
     } else {
@@ -472,10 +621,12 @@ __global__ __launch_bounds__((kLongCols * LongShape<LOGA>::T)) void k_long_cols(
     }
   } else {
     const float* src = a.in_f32 + (int64_t)row * a.n_samp + s0;
-    if (full && ((uintptr_t)src & 7u) == 0) {
+    if (full) {
 #pragma unroll
-      for (int e = 0; e < E; ++e)
-        v[e] = reinterpret_cast<const float2*>(src)[at + ((int64_t)(t + T * e) << log_b)];
+      for (int e = 0; e < E; ++e) {
+        const SamplePair x = reinterpret_cast<const SamplePair*>(src)[at + ((int64_t)(t + T * e) << log_b)];
+        v[e] = make_float2(x.a, x.b);
+      }
     } else {
 #pragma unroll
       for (int e = 0; e < E; ++e) {
@@ -738,9 +889,8 @@ template <int LOGN>
 constexpr int fft_loge() {
   return LOGN >= 15 ? 5 : (LOGN >= 12 ? 4 : 3);
 }
-// The inverse of 2^15 points spills less with 64 points in each of 512 threads (measured
-// 8.61 -> 7.95 ms on 2048 x 21 series); the forward transform, which also unpacks and sums
-// L1 norms, is faster with 32 points in each of 1024 threads.
+// The inverse of 2^15 points holds 64 points in each of 512 threads (c2r_32k_body); the forward
+// transform, which also unpacks and sums L1 norms, is faster with 32 points in each of 1024 threads.
 template <int LOGN>
 constexpr int fft_loge_inv() {
   return LOGN >= 15 ? 6 : fft_loge<LOGN>();
