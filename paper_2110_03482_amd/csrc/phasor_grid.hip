@@ -29,7 +29,7 @@
 //    channel moves far.  From that order every lane gets two runs of channels whose 8 points never
 //    meet another lane's in the same step, so the sums are plain read, add and write in LDS and are
 //    formed in the same order in every run.  (LDS float atomics take about 240 cycles per wave
-//    instruction here: 69 ms where this order takes 13 ms, 1024 channels, 2048 trials, 17 chunks of
+//    instruction here: 69 ms where this order takes 14 ms, 1024 channels, 2048 trials, 21 chunks of
 //    65536 samples.)
 //  - The values of the next columns are loaded during the transform, put into LDS during the
 //    hand-over and read from there in the lane's order; with more than 16 steps per column group
@@ -38,9 +38,9 @@
 //    over the rest, with one exchange through LDS between them; of the second pass only the quarter
 //    of the outputs at each end is wanted, and the workgroup writes them row by row through LDS.
 // Bound: instruction issue and LDS latency of one wave per SIMD (VALU 37 % and LDS 39 % of the
-// cycles; the waits are what is left).  At 1024 channels, 2048 trials, 17 chunks of 65536 samples,
-// float32: 13.4 ms (matrix product 94 ms; reading X and writing Y once takes 2.9 ms); 512 channels,
-// 2048 trials, one chunk of 2^22 samples, powers: 36.8 ms (113 ms).
+// cycles; the waits are what is left).  At 1024 channels, 2048 trials, 21 chunks of 65536 samples,
+// float32: 13.6 to 14.4 ms (matrix product 104 ms; reading X and writing Y once takes 3.6 ms); 512
+// channels, 2048 trials, one chunk of 2^22 samples, powers: 36.7 ms (113 ms).
 #include <cmath>
 
 #include "device_math.h"
@@ -51,6 +51,63 @@ namespace fdd {
 
 namespace {
 constexpr int kGXcds = 8;
+
+// The work of a launch in units (a bin block and a part of its column groups): n_main of them are the
+// first bb_main bin blocks in `split` parts each, whole rounds of the workgroups, and n_tail the other
+// bb_tail bin blocks in tail_split parts.  (There are 2^k + 1 bins: with all blocks cut alike, the last
+// one would be a round of its own: 200 channels, 301 trials, 15 chunks of 8192 samples 405 -> 373 us per
+// call, 1024 channels, 2048 trials, 21 chunks of 65536 22.2 -> 21.6 ms.)  In both, each XCD has a contiguous range of at most main_xcd or
+// tail_xcd units, bin blocks fastest, and its workgroups take neighbouring ones.
+struct GridWork {
+  int n_main, bb_main, split, main_xcd;
+  int n_tail, bb_tail, tail_split, tail_xcd;
+};
+struct GridUnit {
+  int bb, part, parts;
+};
+__host__ __device__ inline GridUnit grid_unit(const GridWork& w, int unit) {
+  if (unit < w.n_main) return {unit % w.bb_main, unit / w.bb_main, w.split};
+  const int t = unit - w.n_main;
+  return {w.bb_main + t % w.bb_tail, t / w.bb_tail, w.tail_split};
+}
+// Unit i of a workgroup (0, 1, ..), or -1 past the last.
+__host__ __device__ inline int grid_nth(const GridWork& w, int xcd, int slot, int n_slot, int i) {
+  const int m0 = w.main_xcd * xcd, m1 = w.n_main < m0 + w.main_xcd ? w.n_main : m0 + w.main_xcd;
+  const int n = m0 + slot < m1 ? (m1 - m0 - slot + n_slot - 1) / n_slot : 0;   // main units of this workgroup
+  if (i < n) return m0 + slot + i * n_slot;
+  const int t0 = w.tail_xcd * xcd, t1 = w.n_tail < t0 + w.tail_xcd ? w.n_tail : t0 + w.tail_xcd;
+  const int t = t0 + slot + (i - n) * n_slot;
+  return t < t1 ? w.n_main + t : -1;
+}
+// The plan of n_bb bin blocks of n_it column groups on `blocks` workgroups: enough units that every
+// workgroup has several, without cutting finer than a column group, and the tail cut so that it ends
+// soonest (a unit also makes the entries of its bins, about a third of a column group's time).
+inline GridWork grid_work(int n_bb, int n_it, int blocks) {
+  GridWork w = {};
+  w.split = 1;
+  while (w.split < n_it && (int64_t)n_bb * w.split < 4 * blocks) ++w.split;
+  int step = blocks;                                 // bin blocks whose units are whole rounds
+  for (int d = 2; d <= w.split; d *= 2)
+    if (w.split % d == 0 && step % 2 == 0) step /= 2;
+  w.bb_main = n_bb / step * step;
+  w.n_main = w.bb_main * w.split;
+  w.main_xcd = w.n_main / kGXcds;
+  w.bb_tail = n_bb - w.bb_main;
+  if (w.bb_tail > 0) {
+    int best = -1;
+    for (int ts = w.split; ts <= n_it && ts <= 4096; ++ts) {
+      const int64_t units = (int64_t)w.bb_tail * ts, xcd = (units + kGXcds - 1) / kGXcds;
+      const int64_t rounds = (xcd + blocks / kGXcds - 1) / (blocks / kGXcds);
+      const int64_t cost = rounds * (3 * ((n_it + ts - 1) / ts) + 1);
+      if (best >= 0 && cost >= best) continue;
+      best = (int)(cost < 0x7fffffff ? cost : 0x7fffffff);
+      w.tail_split = ts;
+    }
+    w.n_tail = w.bb_tail * w.tail_split;
+    w.tail_xcd = (w.n_tail + kGXcds - 1) / kGXcds;
+  }
+  return w;
+}
 // Bins (waves) per workgroup.
 template <bool POWER>
 constexpr int grid_bins() {
@@ -270,7 +327,7 @@ __global__ __launch_bounds__(64) void k_grid_order(GridArgs a) {
 // NS > 0: at most NS (16) schedule steps, the values of a column staged in channel order; NS = 0: any
 // number, every value read where its step needs it.
 template <int LOGM, int NS, bool POWER>
-__global__ __launch_bounds__(64 * grid_bins<POWER>(), 1) void k_phasor_grid(GridArgs a, int n_bb, int n_split, int per_xcd) {
+__global__ __launch_bounds__(64 * grid_bins<POWER>(), 1) void k_phasor_grid(GridArgs a, GridWork work) {
   using S = GridShape<LOGM>;
   constexpr int FB = grid_bins<POWER>();
   constexpr int M = S::M, LM = S::LM, C = S::C, GP = S::GP, XP = S::XP, GL = S::GL;
@@ -289,12 +346,10 @@ __global__ __launch_bounds__(64 * grid_bins<POWER>(), 1) void k_phasor_grid(Grid
   const uint32_t inv_q = (uint32_t)(0xffffffffu / (uint32_t)q) + 1u;   // q = 1 is apart
   uint4* const sched = a.sched + ((int64_t)blockIdx.x * FB + wave) * a.sched_len;   // of this wave (NS = 0)
 
-  // The unit sequence of this workgroup: unit = (split of the iterations, bin block), bin block
-  // fastest; each XCD owns a contiguous range and its workgroups take neighbouring units.
+  // the units of this workgroup
   const int xcd = (int)blockIdx.x % kGXcds, slot = (int)blockIdx.x / kGXcds, n_slot = (int)gridDim.x / kGXcds;
-  const int n_unit = n_bb * n_split;
-  const int u_end = min(n_unit, (xcd + 1) * per_xcd);
-  int unit = xcd * per_xcd + slot;
+  int nth = 0, unit = grid_nth(work, xcd, slot, n_slot, 0);
+  if (unit < 0) return;                              // the whole workgroup, before any barrier
 
   // twiddles of the second pass, exp(2 pi i l k1 / M) with k1 = lane
   // (l = TB la + lb: two short tables and a product instead of 2 LM registers)
@@ -345,19 +400,21 @@ __global__ __launch_bounds__(64 * grid_bins<POWER>(), 1) void k_phasor_grid(Grid
       at[S::RP] = make_float2(raw[i].z, raw[i].w);
     }
   };
-  auto first_col = [&](int u) { return (int)((int64_t)n_it * (u / n_bb) / n_split) % groups * C; };
+  auto first_col = [&](const GridUnit& u) { return (int)((int64_t)n_it * u.part / u.parts) % groups * C; };
   if constexpr (NS > 0) {
-    const int u = min(unit, n_unit - 1);
-    load_raw(first_col(u), u % n_bb * FB);
+    const GridUnit u = grid_unit(work, unit);
+    load_raw(first_col(u), u.bb * FB);
     put_raw();
     grid_barrier();
   }
-  for (; unit < u_end; unit += n_slot) {
-    const int bb = unit % n_bb, sp = unit / n_bb;
+  for (int next; unit >= 0; unit = next) {
+    next = grid_nth(work, xcd, slot, n_slot, ++nth);
+    const GridUnit un = grid_unit(work, unit);
+    const int bb = un.bb, sp = un.part;
     const int f0 = bb * FB;
     // a wave past the last bin repeats it (its row pieces fall into the padding of Y)
     const int f = min(f0 + wave, (POWER ? a.n_pow_bins : a.n_bins) - 1);
-    const int itb = (int)((int64_t)n_it * sp / n_split), ite = (int)((int64_t)n_it * (sp + 1) / n_split);
+    const int itb = (int)((int64_t)n_it * sp / un.parts), ite = (int)((int64_t)n_it * (sp + 1) / un.parts);
     // The schedule of a bin.  The channels in order of their place on the grid are cut into 2 LM
     // equal parts of q, two per lane of a column; in step i every lane adds the i-th channel of both,
     // so the channels added together are q places of the order apart and their 8 points do not meet
@@ -550,9 +607,9 @@ __global__ __launch_bounds__(64 * grid_bins<POWER>(), 1) void k_phasor_grid(Grid
           }
         }
         if constexpr (NS > 0) {
-          const int nu = unit + n_slot < u_end ? unit + n_slot : unit;   // (the last one loads in vain)
+          const GridUnit nu = grid_unit(work, next >= 0 ? next : unit);   // (the last one loads in vain)
           const bool same = it + 1 < ite;
-          load_raw(same ? (it + 1) % groups * C : first_col(nu), same ? f0 : nu % n_bb * FB);
+          load_raw(same ? (it + 1) % groups * C : first_col(nu), same ? f0 : nu.bb * FB);
         }
       }
       wave_order();
@@ -683,15 +740,10 @@ hipError_t launch_grid_ns(const GridArgs& a, hipStream_t st) {
   constexpr int kBlocks = kGridWaves / FB;           // four waves per CU
   const int n_bb = ((POWER ? a.n_pow_bins : a.n_bins) + FB - 1) / FB;
   const int n_it = ((a.n_chunks + C - 1) / C) * a.n_blk;
-  // enough units that every CU has several, without cutting the columns of a bin finer than that
-  int n_split = 1;
-  while (n_split < n_it && (int64_t)n_bb * n_split < 4 * kBlocks) ++n_split;
-  const int64_t units = (int64_t)n_bb * n_split;
-  if (units > 0x3fffffff) return hipErrorInvalidValue;
-  const int per_xcd = (int)((units + kGXcds - 1) / kGXcds);
-  const int slots = per_xcd < kBlocks / kGXcds ? per_xcd : kBlocks / kGXcds;
-  hipLaunchKernelGGL((k_phasor_grid<LOGM, NS, POWER>), dim3((unsigned)(kGXcds * slots)), dim3(64 * FB), 0, st, a, n_bb,
-                     n_split, per_xcd);
+  const GridWork w = grid_work(n_bb, n_it, kBlocks);
+  const int most = w.main_xcd > w.tail_xcd ? w.main_xcd : w.tail_xcd;
+  const int slots = most < kBlocks / kGXcds ? most : kBlocks / kGXcds;
+  hipLaunchKernelGGL((k_phasor_grid<LOGM, NS, POWER>), dim3((unsigned)(kGXcds * slots)), dim3(64 * FB), 0, st, a, w);
   return hipGetLastError();
 }
 
@@ -742,7 +794,7 @@ void grid_divisors(int log_m, std::vector<float>* out) {
   const TapTable t{};
   const int half = 1 << (log_m - 1);
   out->resize((size_t)half);
-  for (int idx = 0; idx < half; ++idx) {
+  for (int idx = half / 2; idx <= half; ++idx) {      // even in idx - half / 2
     const double om = 2.0 * 3.14159265358979323846 * (double)(idx - half / 2) / (double)(2 * half);
     double sum = 0.0;
     for (int i = 0; i < 4; ++i)
@@ -752,7 +804,8 @@ void grid_divisors(int log_m, std::vector<float>* out) {
         for (int d = 7; d >= 0; --d) p = p * r + (double)t.c[i][d];
         sum += 2.0 * wt * p * std::cos(om * ((double)i - 3.5 - r));   // taps i and 7 - i
       }
-    (*out)[(size_t)idx] = (float)(1.0 / sum);
+    if (idx < half) (*out)[(size_t)idx] = (float)(1.0 / sum);
+    (*out)[(size_t)(half - idx)] = (float)(1.0 / sum);
   }
 }
 
