@@ -63,6 +63,7 @@ KERNEL_SOURCES = {
     "facw_f32": "paper_2110_03482_amd/csrc/phasor_facw.hip",
     "facw_f16_split": "paper_2110_03482_amd/csrc/phasor_facw.hip",
     "facw_bf16_split": "paper_2110_03482_amd/csrc/phasor_facw.hip",
+    "grid": "paper_2110_03482_amd/csrc/phasor_grid.hip",
 }
 
 
@@ -86,6 +87,22 @@ def measured_traffic(kernel: str, workload: str):
     if rec is None or rec.get("source_sha") != source_digest(KERNEL_SOURCES[kernel]):
         return None
     return rec.get("bytes_per_launch")
+
+
+def running_kernel(plan) -> str:
+    """The phasor-sum kernel that a plan runs: the grid kernel, or the one of its family."""
+    return "grid" if plan.grid[0] > 0 else plan.kernel
+
+
+def grid_roofline(flops: float, nbytes: float, ms: float, key: str) -> dict:
+    """The grid kernel takes another path to the sums (a Fourier transform along the trial axis), so its
+    work isn't the flops of the matrix product (given for comparison).  What it cannot do without is
+    reading the spectra and writing the sums once."""
+    achieved = nbytes / (ms * 1e-3) / 1e9
+    return {"kernel": "phasor_sum_grid", "bound": "memory", "achieved": achieved, "peak": PEAK["hbm_GBs"],
+            "unit": "GB/s", "frac": achieved / PEAK["hbm_GBs"], "traffic": measured_traffic("grid", key),
+            "algorithmic_bytes_per_launch": nbytes, "matrix_product_flops": flops,
+            "matrix_product_equivalent_TFLOPs": flops / (ms * 1e-3) / 1e12}
 
 
 def make_paper_input(w, fdd):
@@ -305,7 +322,7 @@ def periodicity_form(args, dev, prec: str, with_scaled: bool) -> dict:
     achieved = flops / (stage_ms[2] * 1e-3) / 1e12
     peak = PEAK["fp32_mfma_TFLOPs"] if prec == "fp32" else PEAK["fp16_mfma_TFLOPs"]
     config = {"workload": w.name + f"_{args.mode}_power", "n_chan": w.n_chan, "n_samp": w.n_samp, "n_dm": w.n_dm,
-              "chunk_len": int(g.chunk_len), "precision": prec, "phasor_kernel": plan.kernel}
+              "chunk_len": int(g.chunk_len), "precision": prec, "phasor_kernel": running_kernel(plan)}
     # detection check: the pulsar's harmonic sum (8 harmonics of 33 ms) peaks at trial 467 (DM 57.02)
     f1 = w.n_samp / (33.0e-3 / w.tsamp_s)
     idx = [c for h in range(1, 9) for c in range(int(round(h * f1)) - 2, int(round(h * f1)) + 3)]
@@ -317,6 +334,9 @@ def periodicity_form(args, dev, prec: str, with_scaled: bool) -> dict:
                          "traffic": measured_traffic(plan.kernel, f"{config['workload']}_{prec}"),
                          "algorithmic_flops_per_launch": flops},
             "pulsar_trial": trial}
+    if running_kernel(plan) == "grid":
+        nbytes = w.n_samp // 2 * (8.0 * w.n_chan + 4.0 * w.n_dm)
+        form["roofline"] = grid_roofline(flops, nbytes, stage_ms[2], f"{config['workload']}_{prec}")
     plan.close()
     if with_scaled:
         form["scaled"] = {f"scaled_dm_{p}": run_scaled(args, dev, w, xd, out, flops, p) for p in ("fp32", "fp16_split")}
@@ -547,7 +567,7 @@ def main() -> int:
         g = plan.geometry
         shape = (int(g.out_samples),) if plan.downsampled else (w.n_dm, w.n_samp)
         out = torch.empty(shape, dtype=torch.float32, device=dev)
-        log(f"{precision}: L={g.chunk_len} S={g.stride} D={g.overlap} chunks={g.n_chunks} kernel={plan.kernel} "
+        log(f"{precision}: L={g.chunk_len} S={g.stride} D={g.overlap} chunks={g.n_chunks} kernel={running_kernel(plan)} "
             f"segments={g.n_segments} workspace={g.workspace_bytes / 2**30:.2f} GiB")
         for i in range(args.warmup):
             plan.execute(xd, out)
@@ -563,7 +583,7 @@ def main() -> int:
         stage_ms, n_prof = plan.stage_ms()
         ms = (t1 - t0) * 1e3 / args.steps
         log(f"{precision}: timed {args.steps} steps: {ms:.3f} ms/step; stages {stage_ms} ({n_prof} calls)")
-        res = {"precision": precision, "kernel": plan.kernel, "ms_per_step": ms, "value": samples / (ms * 1e-3),
+        res = {"precision": precision, "kernel": running_kernel(plan), "ms_per_step": ms, "value": samples / (ms * 1e-3),
                "stages_ms": {"transpose": stage_ms[0], "forward_fft": stage_ms[1], "phasor_sum": stage_ms[2],
                              "inverse_fft": stage_ms[3]},
                "geometry": g, "factors": factors,
@@ -611,10 +631,17 @@ def main() -> int:
 
     def roofline(form: dict) -> dict:
         flops = form_flops(form)
+        wl = w.name + f"_{args.mode}_{form['precision']}" + ("" if form["factors"] is None else "_downsampled")
+        if form["kernel"] == "grid":
+            n_dm_bins = flops / (8.0 * w.n_chan * form["geometry"].n_chunks)      # (trial, bin) pairs of a chunk
+            runs = int(form["geometry"].n_segments)
+            spectra = sum((int(form["geometry"].chunk_len) // (2 * int(d)) + 1)
+                          for d in (np.unique(form["factors"]) if form["factors"] is not None else [1] * runs))
+            nbytes = 8.0 * form["geometry"].n_chunks * (w.n_chan * spectra + n_dm_bins)
+            return grid_roofline(flops, nbytes, form["stages_ms"]["phasor_sum"], wl)
         achieved = flops / (form["stages_ms"]["phasor_sum"] * 1e-3) / 1e12
         peak = {"fp32": PEAK["fp32_mfma_TFLOPs"], "fp16_split": PEAK["fp16_mfma_TFLOPs"],
                 "bf16_split": PEAK["bf16_mfma_TFLOPs"]}[form["precision"]]
-        wl = w.name + f"_{args.mode}_{form['precision']}" + ("" if form["factors"] is None else "_downsampled")
         r = {"kernel": f"phasor_sum_{form['kernel']}", "bound": "alu" if form["kernel"] == "valu" else "mfma",
              "achieved": achieved, "peak": peak, "unit": "TFLOP/s", "frac": achieved / peak,
              "traffic": measured_traffic(form["kernel"], wl), "algorithmic_flops_per_launch": flops}

@@ -56,8 +56,9 @@ constexpr int kGXcds = 8;
 // first bb_main bin blocks in `split` parts each, whole rounds of the workgroups, and n_tail the other
 // bb_tail bin blocks in tail_split parts.  (There are 2^k + 1 bins: with all blocks cut alike, the last
 // one would be a round of its own: 200 channels, 301 trials, 15 chunks of 8192 samples 405 -> 373 us per
-// call, 1024 channels, 2048 trials, 21 chunks of 65536 22.2 -> 21.6 ms.)  In both, each XCD has a contiguous range of at most main_xcd or
-// tail_xcd units, bin blocks fastest, and its workgroups take neighbouring ones.
+// call, 1024 channels, 2048 trials, 21 chunks of 65536 22.2 -> 21.6 ms.)  In both, each XCD has a
+// contiguous range of at most main_xcd or tail_xcd units, bin blocks fastest, and its workgroups take
+// neighbouring ones.
 struct GridWork {
   int n_main, bb_main, split, main_xcd;
   int n_tail, bb_tail, tail_split, tail_xcd;
