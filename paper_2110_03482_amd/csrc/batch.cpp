@@ -284,7 +284,7 @@ hipError_t launch_grid_stack(const fdd_batch_s* b, const Stack& sk, hipStream_t 
     a.window = r.window;
     a.n_bins = (int)p->n_bins;
     a.pitch = p->pitch;
-    grid_set_scratch(&a, b->d_tab + b->sched, p->desc.n_chan, p->n_bins);
+    grid_set_scratch(&a, b->d_tab + b->sched, p->desc.n_chan, grid_scratch_bins(p, r));
     const hipError_t e = launch_phasor_grid(a, st);
     if (e != hipSuccess) return e;
   }

@@ -129,7 +129,7 @@ hipError_t launch_grid_run(fdd_plan_t p, const GridRun& r, const PhasorArgs& all
   a.n_pow_bins = s.n_pow_bins;
   a.pitch = s.pitch;
   a.dc_add = s.dc_add;
-  grid_set_scratch(&a, p->d_ws + p->ws.sched, s.n_chan, p->L / p->segs[(size_t)r.seg].factor / 2 + 1);
+  grid_set_scratch(&a, p->d_ws + p->ws.sched, s.n_chan, grid_scratch_bins(p, r));
   return launch_phasor_grid(a, st);
 }
 

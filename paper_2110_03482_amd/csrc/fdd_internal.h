@@ -105,6 +105,7 @@ struct GridArgs {
   int* turns = nullptr;             // [groups of bins], and
   float4* dump = nullptr;           // 16 bytes per lane that nobody reads
   int sched_len = 0;
+  int64_t n_groups = 0;             // groups of bins that places and turns have room for
   uint64_t inc_min = 0, inc_max = 0; // smallest and largest turns per bin of one DM step
   uint64_t gap[kGridGaps] = {};     // smallest difference of the turns of channels 2^j parts of the
                                     // order apart (a part: half a lane's share of the channels); ~0: none
@@ -341,11 +342,12 @@ inline size_t grid_order_bytes(int n_chan, int64_t n_bins, int log_gb) {
   return (size_t)grid_groups(n_bins, log_gb) * (sizeof(int) + (size_t)grid_sched_len(n_chan) * sizeof(uint16_t));
 }
 inline void grid_set_scratch(GridArgs* a, uint8_t* mem, int n_chan, int64_t n_bins) {
+  a->n_groups = grid_groups(n_bins, a->log_gb);
   a->sched_len = grid_sched_len(n_chan);
   a->sched = (uint4*)mem;
   a->dump = (float4*)(a->sched + (size_t)kGridWaves * (size_t)a->sched_len);
   a->turns = (int*)(mem + grid_sched_bytes(n_chan));
-  a->places = (uint16_t*)(a->turns + grid_groups(n_bins, a->log_gb));
+  a->places = (uint16_t*)(a->turns + a->n_groups);
 }
 hipError_t launch_phasor_grid(const GridArgs& a, hipStream_t st);
 void grid_divisors(int log_m, std::vector<float>* out);
@@ -474,6 +476,8 @@ void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out);
 // family of the plan is the faster one.
 bool fac_few_pays(const fdd_plan_s* p, int64_t n_chunks);
 bool grid_runs(const fdd_plan_s* p, int n_chunks, std::vector<GridRun>* out);
+// Bins that the scratch of a run is laid out for, and its bytes.
+int64_t grid_scratch_bins(const fdd_plan_s* p, const GridRun& r);
 size_t grid_scratch_bytes(const fdd_plan_s* p, const GridRun& r);
 // Channels by ascending delay.
 void grid_order(const fdd_plan_s* p, std::vector<int>* out);

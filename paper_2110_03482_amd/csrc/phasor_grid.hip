@@ -779,7 +779,8 @@ hipError_t launch_phasor_grid(const GridArgs& a, hipStream_t st) {
       a.places == nullptr || a.turns == nullptr || a.dump == nullptr || a.sched_len < grid_sched_len(a.n_chan) || a.window < 2 ||
       (a.Yc == nullptr) == (a.P == nullptr) || a.n_dm < 1 || a.n_chan < 1 || a.n_chan > 65535 || a.n_chunks < 1 ||
       a.blk < 1 || 2 * a.blk > (1 << a.log_m) || (int64_t)a.n_blk * a.blk < a.n_dm || (a.n_blk > 1 && a.log_m != 12) ||
-      (a.P != nullptr && (a.n_chunks != 1 || a.log_m != 12)))
+      (a.P != nullptr && (a.n_chunks != 1 || a.log_m != 12)) ||
+      grid_groups(a.P != nullptr ? a.n_pow_bins : a.n_bins, a.log_gb) > a.n_groups)
     return hipErrorInvalidValue;
   return launch_grid_m(a, st);
 }

@@ -245,10 +245,15 @@ bool fac_few_pays(const fdd_plan_s* p, int64_t n_chunks) {
   return (int64_t)p->desc.n_dm * n_chunks <= most;
 }
 
+// The most bins of one run's launches: those that its segment's inverse reads, but all of them where
+// the plan gives power spectra as well (down-sampling does not apply to those).
+int64_t grid_scratch_bins(const fdd_plan_s* p, const GridRun& r) {
+  return p->desc.single_chunk ? p->n_bins : p->L / p->segs[(size_t)r.seg].factor / 2 + 1;
+}
+
 // Scratch of one run's launches.
 size_t grid_scratch_bytes(const fdd_plan_s* p, const GridRun& r) {
-  const int64_t bins = p->L / p->segs[(size_t)r.seg].factor / 2 + 1;
-  return grid_sched_bytes(p->desc.n_chan) + grid_order_bytes(p->desc.n_chan, bins, r.log_gb);
+  return grid_sched_bytes(p->desc.n_chan) + grid_order_bytes(p->desc.n_chan, grid_scratch_bins(p, r), r.log_gb);
 }
 
 // The plan's trials as runs of equal steps (as uniform_grid tests them), each inside one segment;
