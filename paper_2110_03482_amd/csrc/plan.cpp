@@ -192,34 +192,28 @@ void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out) 
   }
 }
 
-// Whether the grid kernel is expected to be faster than the plan's family: a model of both, from
-// measured times of 260 shapes (4096 to 65536 samples a chunk, 1 to 20 chunks, 32 to 1024 channels,
-// 64 to 2048 trials).  The grid kernel: a column group (its transform, stores and up to 8 or 16
-// spread steps) costs kRoundUs and runs on 512 workgroups at a time, more steps cost kStepUs each on
-// top of a base without staged values, and the entries of a bin kBatchUs per 64 channels; it
-// predicts the measured times within -25 and +30 %.  The direct families: their best measured rates
-// over the work that they really do (whole tiles of trials and columns), so the line lies where the
-// grid wins with the direct kernel at its best.  E.g. 8192 samples, 20 chunks: 200 channels and 256
-// trials 384 us against 449 us (mfma_f32), 128 channels and 128 trials 237 against 161; one chunk of
-// 65536, 2048 trials: 128 channels 468 against 772 us (fac_f32), 64 channels 445 against 445.
+// Whether the grid kernel is expected to be faster than the plan's family: a model of both, fitted to
+// the phasor stage of 786 shapes in both forms (4096 to 2^20 samples a chunk, 1 to 310 chunks, 16 to
+// 1024 channels, 64 to 4096 trials) and checked on 1037 others.
+// The grid kernel: a column group (its transform, stores and up to 8 or 16 spread steps) costs kRoundUs
+// and runs on 512 workgroups at a time, more steps cost kStepUs each on top of a base without staged
+// values, and the entries of a bin kBatchUs per 64 channels.  90 % of the shapes lie within -12 and
+// +10 % of it.  Rows of Y that lie a multiple of 16 KiB apart, N a multiple of 32, share few memory
+// channels where they exceed the last cache: 64 chunks of 16384, 589 trials 7.1 ms against 3.0.
+// The families, per segment: a start, the matrix products of whole tiles (64 trials in the direct
+// kernels and 64 coarse rows of phasor_fac_fine(N) trials in the factorised ones, by whole tiles of 8
+// chunks in the direct ones), the phasors, and the sums written.  90 % lie within -25 and +15 %.
+// Near the line either form may be the faster one, so the grid has to win by kMargin: 841 of the 1823
+// shapes then take it, and 5 of those are slower than their family, by 7 % at most.
+// E.g. two chunks of 65536 (grid, fac): split, 91 channels, 218 trials 407 and 267 us; 164 channels, 360
+// trials 459 and 453; 256 channels, 316 trials 470 and 651; FP32, 52 channels, 388 trials 427 and 323;
+// 105 channels, 139 trials 410 and 592.
 static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& runs) {
-  constexpr double kRoundUs[2] = {12.9, 17.7}, kBaseUs = 11.6, kStepUs = 0.467, kBatchUs = 0.266, kStartUs = 11.0;
-  constexpr double kBlocks = 512.0;
+  constexpr double kRoundUs[2] = {11.5, 13.9}, kBaseUs = 10.0, kStepUs = 0.405, kBatchUs = 0.47, kStartUs = 20.0;
+  constexpr double kBlocks = 512.0, kMargin = 1.1, kApart = 1.6;
   const int n_chan = p->desc.n_chan;
+  const bool apart = N % 32 == 0 && (double)p->desc.n_dm * (double)N * (double)p->pitch * 8.0 > 256e6;
   double grid = 0.0, direct = 0.0;
-  const bool fp32 = p->desc.precision == FDD_FP32;
-  const bool fac = p->fac_fine > 0 && p->facw_nt == 0;
-  // TFLOP/s of the family, and its smallest tile of trials and channels
-  double rate = fp32 ? 100.0 : 140.0;
-  int dm_tile = 64, min_chan = 64, col_tile = 8;
-  if (p->facw_nt > 0) {
-    rate = 240.0, dm_tile = 128, min_chan = 96, col_tile = 1;
-  } else if (p->fac_few || p->kernel == "valu") {
-    rate = 20.0, dm_tile = 4, min_chan = 1, col_tile = 1;
-  } else if (fac) {
-    rate = fp32 ? 92.0 : 170.0, dm_tile = 2048, min_chan = 1, col_tile = 1;
-  }
-  const auto up = [](int n, int to) { return (double)((n + to - 1) / to * to); };
   for (const GridRun& r : runs) {
     const double bins = (double)(p->L / p->segs[(size_t)r.seg].factor / 2 + 1);
     const int lm = 1 << (r.log_m - 6), per = 64 / lm;
@@ -229,10 +223,35 @@ static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& ru
     const double setups = std::max(1.0, std::ceil(pairs * r.n_blk / kBlocks));
     const int steps = 2 * ((n_chan + 2 * lm - 1) / (2 * lm));
     const double round = steps <= 8 ? kRoundUs[0] : steps <= 16 ? kRoundUs[1] : kBaseUs + kStepUs * steps;
-    grid += kStartUs + rounds * round + setups * kBatchUs * (double)((n_chan + 63) / 64);
-    direct += 6.0 + 8.0 * up(r.n, dm_tile) * (double)std::max(n_chan, min_chan) * bins * up(N, col_tile) / (rate * 1e6);
+    grid += kStartUs + rounds * (apart ? kApart * round : round) + setups * kBatchUs * (double)((n_chan + 63) / 64);
   }
-  return grid < direct;
+  const auto up = [](int64_t n, int64_t to) { return (double)((n + to - 1) / to * to); };
+  const bool fp32 = p->desc.precision == FDD_FP32;
+  const bool fac = p->fac_fine > 0 && p->facw_nt == 0 && N <= 2;
+  const bool vec = fac ? p->fac_few && fac_few_pays(p, N) : p->kernel == "valu" && (N <= 2 || p->n_chunks > 2);
+  const int groups = chunk_groups(N);
+  double cols = 0.0;
+  for (int g = 0; g < groups; ++g) cols += up(N / groups + (g < N % groups ? 1 : 0), 8);
+  for (const Segment& sg : p->segs) {
+    const double bins = (double)(p->L / sg.factor / 2 + 1);
+    const double sums = 1e-6 * (double)sg.n * (double)N * bins;        // in millions, as what follows
+    const double rows = 1e-6 * bins * (double)n_chan;
+    if (vec) {
+      direct += 20.0 + up(sg.n, 4) * rows * (0.242 * N + 0.197);
+    } else if (fac) {
+      const double tile = 64.0 * phasor_fac_fine(N);
+      const double work = 1e-6 * std::ceil(bins / 4.0) * std::ceil((double)sg.n / tile) * (double)n_chan;
+      direct += fp32 ? 20.0 + 640.0 * work + 1.21 * sums : 17.0 + 310.0 * work + 2.09 * sums;
+    } else if (p->facw_nt > 0) {
+      direct += 16.0 + up(sg.n, 64) * rows * (0.0341 * N + 0.0207 * groups) + 2.78 * sums;
+    } else if (fp32) {
+      direct += 12.0 + up(sg.n, 64) * rows * 0.0698 * cols + 2.86 * sums;
+    } else {
+      const double w = up(sg.n, 64) * rows * (0.0418 * cols + 0.030 * groups) + 2.47 * sums;
+      direct += 14.0 + (p->desc.precision == FDD_FP16_SPLIT ? 0.94 * w : w);
+    }
+  }
+  return kMargin * grid < direct;
 }
 
 // Few trials leave most of the 64 coarse rows of a workgroup of the factorised kernels idle (their

@@ -23,3 +23,49 @@ def test_scratch_of_a_down_sampled_single_chunk_plan_holds_all_bins(L, dm_max, f
     with dry(64, L, dms, L, single_chunk=True, downsample=[factor] * 1024) as p:
         assert p.grid[0] == 1
         assert p.geometry.workspace_bytes >= full + 8 * (L // factor)
+
+
+# Measured phasor stages of both forms on an MI355X, us (family, grid): chunks, L, channels, trials, precision.
+# A single chunk is a circular transform, two are 1.25 L samples.
+MEASURED = [
+    # the factorised kernels are the faster ones: a workgroup has 64 coarse rows of 32 / N trials
+    (2, 1 << 16, 91, 218, "fp16_split", 267, 407), (2, 1 << 16, 93, 830, "bf16_split", 343, 442),
+    (2, 1 << 16, 128, 192, "fp16_split", 346, 429), (2, 1 << 14, 91, 535, "bf16_split", 92, 127),
+    (2, 1 << 15, 83, 106, "fp16_split", 138, 216), (2, 1 << 12, 118, 132, "bf16_split", 39, 58),
+    (2, 1 << 16, 77, 2216, "bf16_split", 886, 1430), (2, 1 << 16, 52, 388, "fp32", 323, 427),
+    (2, 1 << 14, 48, 129, "fp32", 84, 124), (2, 1 << 13, 51, 288, "fp32", 59, 80), (2, 1 << 16, 40, 3022, "fp32", 911, 1490),
+    # the grid is
+    (2, 1 << 16, 256, 316, "bf16_split", 651, 470), (2, 1 << 16, 195, 1065, "fp16_split", 1144, 765),
+    (2, 1 << 16, 105, 139, "fp32", 592, 410), (2, 1 << 16, 117, 1681, "fp32", 1313, 816),
+    (1, 1 << 13, 359, 1999, "fp32", 311, 105), (2, 1 << 15, 163, 968, "fp32", 480, 289)]
+
+
+@pytest.mark.parametrize("case", MEASURED, ids=[f"{c[2]}ch_{c[3]}dm_L{c[1]}x{c[0]}_{c[4]}" for c in MEASURED])
+def test_rule_takes_the_form_that_measures_faster(case):
+    chunks, L, n_chan, n_dm, precision, family, grid = case
+    top = 0.3 * L * 64e-6 / (4148.808 * (1250.0 ** -2 - 1550.0 ** -2))
+    with dry(n_chan, L if chunks == 1 else L * 5 // 4, np.linspace(0.0, top, n_dm), L, single_chunk=chunks == 1,
+             precision=precision) as p:
+        assert p.geometry.n_chunks == chunks and p.kernel.startswith("fac_")
+        assert (p.grid[0] > 0) == (grid < family)
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp16_split"])
+def test_rule_over_trials_of_two_chunks(precision):
+    """The line is the fewest channels that take the grid.  Up to 1024 trials both forms do the same
+    work, but the families write more sums, so the line falls.  With twice the trials past 1024 both
+    forms do twice the work, but for a bin's entries, which the grid kernel makes once (27 of 450 us
+    against at least 190 us of products: 14 %), so the line stays, within that and the 4 channels of
+    the search."""
+    L = 1 << 16
+
+    def line(n_dm):
+        for n_chan in range(16, 400, 4):
+            with dry(n_chan, L * 5 // 4, np.linspace(0.0, 500.0, n_dm), L, precision=precision) as p:
+                if p.grid[0] > 0:
+                    return n_chan
+        return 400
+
+    assert line(300) >= line(600) >= line(1024)
+    for n_dm in (600, 800, 1024):
+        assert abs(line(2 * n_dm) - line(n_dm)) <= 0.14 * line(n_dm) + 4
