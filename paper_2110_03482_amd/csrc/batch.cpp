@@ -209,6 +209,10 @@ const Choice& chosen(const fdd_batch_s* b, const Launch& l) {
 // Candidate kernels of the phasor sum for a plan's precision and chunk count; `fac` adds the
 // DM-factorised kernels (uniform DM grid, exact delays), `few` the vector kernel on their tables.
 // cands[0] is what fdd_execute runs.
+// A choice holds for all batches of the class, whatever their trials, so a class does not offer the
+// vector kernel where the factorised ones are the default: its time grows with the trials, theirs
+// hardly up to 2048, and a choice made at 300 trials doubled the time of a batch of 453 to 1813
+// (64 channels and fewer, chunks of 65536: 1.81 -> 3.37 ms).  Few trials have a class of their own.
 Class make_class(const fdd_plan_s* p, int N, bool fac, bool fac_default, bool few) {
   Class c;
   // the direct matrix-core kernels run over chunk groups of at most kDirectMaxChunks
@@ -225,16 +229,15 @@ Class make_class(const fdd_plan_s* p, int N, bool fac, bool fac_default, bool fe
     c.cands.push_back({kind, 0, true});
   } else if (N == 1) {
     std::snprintf(key, sizeof key, "fp32/L%lld/n1%s", (long long)p->L, fs);
-    c.cands.push_back({kValu, 1, false});
+    if (!fac_default) c.cands.push_back({kValu, 1, false});
   } else {
     // the single plan keeps these on the VALU (few chunks, or rows too long for the kernels'
     // 2 GiB descriptor window)
     const bool small = !phasor_mfma_f32_supported(NG) || !phasor_mfma_f32_window_ok(N, p->pitch);
     std::snprintf(key, sizeof key, "fp32/L%lld/%s%d%s", (long long)p->L, small ? "n" : "nt", small ? N : c.nt, fs);
-    if (small) c.cands.push_back({kValu, 4, false});
-    else
-      for (int v = 0; v < kMfmaF32Variants; ++v)
-        for (int per = 0; per < 2; ++per) c.cands.push_back({kMfmaF32, v, per == 1});
+    if (small && !fac_default) c.cands.push_back({kValu, 4, false});
+    for (int v = 0; v < kMfmaF32Variants && !small; ++v)
+      for (int per = 0; per < 2; ++per) c.cands.push_back({kMfmaF32, v, per == 1});
   }
   if (fac || fac_default) {
     const Choice g{kFac, prec, false}, q{kFac, prec, true};
