@@ -494,8 +494,10 @@ fdd_status enqueue_all(fdd_batch_s* b, const void* const* in, hipStream_t st) {
 // the wave's forward stages run once, then each candidate runs once to warm up and is timed
 // (the best of three when a run is shorter than 50 ms).  A candidate whose warm-up is already
 // kPrune times slower than the class's best timed run so far keeps its warm-up time and is
-// not timed again.  Synchronises the stream.
+// not timed again; kLoadMs of the warm-up don't count, since the first launch of a kernel in a
+// process also loads it (0.9 ms measured).  Synchronises the stream.
 constexpr float kPrune = 1.5f;
+constexpr float kLoadMs = 5.0f;
 
 fdd_status autotune(fdd_batch_s* b, const void* const* in, float* const* out, hipStream_t st) {
   hipEvent_t e0 = nullptr, e1 = nullptr;
@@ -540,7 +542,7 @@ fdd_status autotune(fdd_batch_s* b, const void* const* in, float* const* out, hi
           float ms = 0.0f;
           if (!check(hipEventElapsedTime(&ms, e0, e1), "hipEventElapsedTime")) break;
           if (rep == 0) {                                  // warm-up
-            if (lead > 0.0f && ms > kPrune * lead) {       // clearly slower: keep the warm-up time
+            if (lead > 0.0f && ms > kPrune * lead + kLoadMs) {       // clearly slower: keep the warm-up time
               best = ms;
               break;
             }

@@ -4,6 +4,11 @@ A tuned choice is kept for the class, for later batches of the process and in th
 whatever their trial counts.  So a class must not offer a kernel that only a part of its trial counts
 should run.
 """
+import json
+import os
+import subprocess
+import sys
+
 import numpy as np
 import pytest
 
@@ -36,3 +41,34 @@ def test_factorised_classes_do_not_offer_the_vector_kernel(chunks, monkeypatch, 
     assert any(k.startswith("fac_few/") for k in classes["fac0few"]["candidates"])
     for p in plans:
         p.close()
+
+
+_FRESH = """
+import json
+import numpy as np
+import torch
+import paper_2110_03482_amd as fdd
+n = 1 << 16
+freqs = 1250.0 + (np.arange(64) + 0.5) * (300.0 / 64)
+plans = [fdd.Plan(freqs, 1550.0, 64e-6, np.linspace(0.0, 400.0, 64), n + n // 4, n, precision="fp16_split", workspace=False)
+         for _ in range(2)]
+assert all(p.geometry.n_chunks == 2 and p.grid[0] == 0 for p in plans)
+xs = [torch.randn((64, n + n // 4), device="cuda") for _ in plans]
+with fdd.Batch(plans) as b:
+    b.execute(xs)
+    torch.cuda.synchronize()
+    print(json.dumps(b.describe()["classes"]))
+"""
+
+
+def test_first_launches_in_a_process_do_not_prune_a_candidate():
+    """64 trials and two chunks: the direct split kernel measures 0.4 to 0.6 of the vector kernel's time, which
+    is timed before it.  The direct kernel's first launch also loads it, several times that."""
+    root = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+    r = subprocess.run([sys.executable, "-c", _FRESH], cwd=root, env=dict(os.environ, PYTHONPATH=root), capture_output=True,
+                       text=True, timeout=100)
+    assert r.returncode == 0, r.stderr[-2000:]
+    (c,) = json.loads(r.stdout.strip().splitlines()[-1])
+    print(c["key"], c["choice"], c["candidates"])
+    assert c["key"].endswith("+fac0few")
+    assert c["choice"] == "mfma_f16_split/grid"
