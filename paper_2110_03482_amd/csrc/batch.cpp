@@ -651,8 +651,9 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
     const bool fac_default =
         sk.beams.size() == 1 ? p->fac_fine > 0 && p->facw_nt == 0 : (sk.fine > 0 && sk.n_chunks <= 2);
     const bool few = fac_default && p->fac_few && fac_few_pays(p, sk.n_chunks);
-    // the grid form where fdd_execute takes it (a stack by the same rule for its own chunk count)
-    if (!p->grid.empty()) (void)grid_runs(p, sk.n_chunks, &sk.grid);
+    // the grid form where fdd_execute takes it (a stack by the same rule for its own chunk count); with
+    // autotuning it has to win against the other kernels' shared launch
+    if (!p->grid.empty()) (void)grid_runs(p, sk.n_chunks, n > 1 && !(dd.flags & FDD_BATCH_NO_AUTOTUNE), &sk.grid);
     if (!sk.grid.empty()) sk.fine = sk.coarse = 0;
     Class c = sk.grid.empty() ? make_class(p, sk.n_chunks, sk.fine > 0, fac_default, few) : grid_class(p);
     auto it = class_of.find(c.key);

@@ -473,9 +473,9 @@ void factor_tables(const fdd_plan_s* p, int fine, int coarse, double dm0, double
 // Channel table of a grid run, [n_blk][n_chan].
 void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out);
 // The plan's trials as grid runs for n_chunks chunks; false if they have no such form or the kernel
-// family of the plan is the faster one.
+// family of the plan is the faster one (tuned: or another kernel that an autotuned batch may choose).
 bool fac_few_pays(const fdd_plan_s* p, int64_t n_chunks);
-bool grid_runs(const fdd_plan_s* p, int n_chunks, std::vector<GridRun>* out);
+bool grid_runs(const fdd_plan_s* p, int n_chunks, bool tuned, std::vector<GridRun>* out);
 // Bins that the scratch of a run is laid out for, and its bytes.
 int64_t grid_scratch_bins(const fdd_plan_s* p, const GridRun& r);
 size_t grid_scratch_bytes(const fdd_plan_s* p, const GridRun& r);

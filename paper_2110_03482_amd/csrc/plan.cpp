@@ -208,12 +208,12 @@ void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out) 
 // E.g. two chunks of 65536 (grid, fac): split, 91 channels, 218 trials 407 and 267 us; 164 channels, 360
 // trials 459 and 453; 256 channels, 316 trials 470 and 651; FP32, 52 channels, 388 trials 427 and 323;
 // 105 channels, 139 trials 410 and 592.
-static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& runs) {
+static double grid_us(const fdd_plan_s* p, int N, const std::vector<GridRun>& runs) {
   constexpr double kRoundUs[2] = {11.5, 13.9}, kBaseUs = 10.0, kStepUs = 0.405, kBatchUs = 0.47, kStartUs = 20.0;
-  constexpr double kBlocks = 512.0, kMargin = 1.1, kApart = 1.6;
+  constexpr double kBlocks = 512.0, kApart = 1.6;
   const int n_chan = p->desc.n_chan;
   const bool apart = N % 32 == 0 && (double)p->desc.n_dm * (double)N * (double)p->pitch * 8.0 > 256e6;
-  double grid = 0.0, direct = 0.0;
+  double us = 0.0;
   for (const GridRun& r : runs) {
     const double bins = (double)(p->L / p->segs[(size_t)r.seg].factor / 2 + 1);
     const int lm = 1 << (r.log_m - 6), per = 64 / lm;
@@ -223,35 +223,57 @@ static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& ru
     const double setups = std::max(1.0, std::ceil(pairs * r.n_blk / kBlocks));
     const int steps = 2 * ((n_chan + 2 * lm - 1) / (2 * lm));
     const double round = steps <= 8 ? kRoundUs[0] : steps <= 16 ? kRoundUs[1] : kBaseUs + kStepUs * steps;
-    grid += kStartUs + rounds * (apart ? kApart * round : round) + setups * kBatchUs * (double)((n_chan + 63) / 64);
+    us += kStartUs + rounds * (apart ? kApart * round : round) + setups * kBatchUs * (double)((n_chan + 63) / 64);
   }
+  return us;
+}
+
+enum class Family { kVector, kFactorised, kChunked, kDirect };
+
+// Without the start of its launches (kStartUs of grid_pays).
+static double family_us(const fdd_plan_s* p, int N, Family fam, const Segment& sg) {
   const auto up = [](int64_t n, int64_t to) { return (double)((n + to - 1) / to * to); };
+  const bool fp32 = p->desc.precision == FDD_FP32;
+  const int groups = chunk_groups(N);
+  const double bins = (double)(p->L / sg.factor / 2 + 1);
+  const double sums = 1e-6 * (double)sg.n * (double)N * bins;        // in millions, as what follows
+  const double rows = 1e-6 * bins * (double)p->desc.n_chan;
+  switch (fam) {
+    case Family::kVector: return up(sg.n, 4) * rows * (0.242 * N + 0.197);
+    case Family::kFactorised: {
+      const double tile = 64.0 * phasor_fac_fine(N);
+      const double work = 1e-6 * std::ceil(bins / 4.0) * std::ceil((double)sg.n / tile) * (double)p->desc.n_chan;
+      return fp32 ? 640.0 * work + 1.21 * sums : 310.0 * work + 2.09 * sums;
+    }
+    case Family::kChunked: return up(sg.n, 64) * rows * (0.0341 * N + 0.0207 * groups) + 2.78 * sums;
+    default: break;
+  }
+  double cols = 0.0;
+  for (int g = 0; g < groups; ++g) cols += up(N / groups + (g < N % groups ? 1 : 0), 8);
+  if (fp32) return up(sg.n, 64) * rows * 0.0698 * cols + 2.86 * sums;
+  const double us = up(sg.n, 64) * rows * (0.0418 * cols + 0.030 * groups) + 2.47 * sums;
+  return p->desc.precision == FDD_FP16_SPLIT ? 0.94 * us : us;
+}
+
+// `tuned`: against the best of the kernels that an autotuned batch chooses from, whose beams share a
+// launch, so that its start is no beam's own.
+static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& runs, bool tuned) {
+  constexpr double kMargin = 1.1;
+  constexpr double kStartUs[4] = {20.0, 18.0, 16.0, 13.0};           // by family
   const bool fp32 = p->desc.precision == FDD_FP32;
   const bool fac = p->fac_fine > 0 && p->facw_nt == 0 && N <= 2;
   const bool vec = fac ? p->fac_few && fac_few_pays(p, N) : p->kernel == "valu" && (N <= 2 || p->n_chunks > 2);
-  const int groups = chunk_groups(N);
-  double cols = 0.0;
-  for (int g = 0; g < groups; ++g) cols += up(N / groups + (g < N % groups ? 1 : 0), 8);
-  for (const Segment& sg : p->segs) {
-    const double bins = (double)(p->L / sg.factor / 2 + 1);
-    const double sums = 1e-6 * (double)sg.n * (double)N * bins;        // in millions, as what follows
-    const double rows = 1e-6 * bins * (double)n_chan;
-    if (vec) {
-      direct += 20.0 + up(sg.n, 4) * rows * (0.242 * N + 0.197);
-    } else if (fac) {
-      const double tile = 64.0 * phasor_fac_fine(N);
-      const double work = 1e-6 * std::ceil(bins / 4.0) * std::ceil((double)sg.n / tile) * (double)n_chan;
-      direct += fp32 ? 20.0 + 640.0 * work + 1.21 * sums : 17.0 + 310.0 * work + 2.09 * sums;
-    } else if (p->facw_nt > 0) {
-      direct += 16.0 + up(sg.n, 64) * rows * (0.0341 * N + 0.0207 * groups) + 2.78 * sums;
-    } else if (fp32) {
-      direct += 12.0 + up(sg.n, 64) * rows * 0.0698 * cols + 2.86 * sums;
-    } else {
-      const double w = up(sg.n, 64) * rows * (0.0418 * cols + 0.030 * groups) + 2.47 * sums;
-      direct += 14.0 + (p->desc.precision == FDD_FP16_SPLIT ? 0.94 * w : w);
-    }
+  const Family own = vec ? Family::kVector : fac ? Family::kFactorised : p->facw_nt > 0 ? Family::kChunked : Family::kDirect;
+  double direct = 0.0;
+  if (!tuned) {
+    for (const Segment& sg : p->segs) direct += kStartUs[(int)own] + family_us(p, N, own, sg);
+  } else {
+    const Segment& sg = p->segs[0];
+    direct = family_us(p, N, own == Family::kChunked ? Family::kDirect : own, sg);
+    if (runs.size() == 1 && phasor_fac_fine(N) > 0) direct = std::min(direct, family_us(p, N, Family::kFactorised, sg));
+    if (!fp32) direct = std::min(direct, family_us(p, N, Family::kDirect, sg));
   }
-  return kMargin * grid < direct;
+  return kMargin * grid_us(p, N, runs) < direct;
 }
 
 // Few trials leave most of the 64 coarse rows of a workgroup of the factorised kernels idle (their
@@ -277,7 +299,7 @@ size_t grid_scratch_bytes(const fdd_plan_s* p, const GridRun& r) {
 
 // The plan's trials as runs of equal steps (as uniform_grid tests them), each inside one segment;
 // false if a run is too short for the grid kernel or the plan's delays are rounded.
-bool grid_runs(const fdd_plan_s* p, int N, std::vector<GridRun>* out) {
+bool grid_runs(const fdd_plan_s* p, int N, bool tuned, std::vector<GridRun>* out) {
   out->clear();
   if (p->desc.delay_mode != FDD_DELAY_EXACT) return false;
   double big = 0.0;
@@ -366,7 +388,7 @@ bool grid_runs(const fdd_plan_s* p, int N, std::vector<GridRun>* out) {
       j += n;
     }
   }
-  if (!p->grid_force && !grid_pays(p, N, *out)) out->clear();
+  if (!p->grid_force && !grid_pays(p, N, *out, tuned)) out->clear();
   return !out->empty();
 }
 
@@ -820,7 +842,7 @@ fdd_status fdd_plan(const fdd_plan_desc* desc, fdd_plan_t* out) {
                      std::getenv("FDD_FACTOR") != nullptr ||
                      std::getenv("FDD_TILE_VARIANT") != nullptr || std::getenv("FDD_PHASE_TABLE") != nullptr;
     p->grid_force = ge != nullptr && std::strcmp(ge, "1") == 0;
-    if (!off) (void)grid_runs(p, (int)p->n_chunks, &p->grid);
+    if (!off) (void)grid_runs(p, (int)p->n_chunks, false, &p->grid);
   }
   // spin-frequency-scaled DMs (Eq. 8): first block whose rows stay within the halo
   if (d.flags & FDD_PLAN_SCALED_DM) {

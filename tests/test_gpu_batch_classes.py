@@ -72,3 +72,27 @@ def test_first_launches_in_a_process_do_not_prune_a_candidate():
     print(c["key"], c["choice"], c["candidates"])
     assert c["key"].endswith("+fac0few")
     assert c["choice"] == "mfma_f16_split/grid"
+
+
+@pytest.mark.parametrize("n_chan,tuned", [(360, False), (1000, True)])
+def test_grid_beams_win_against_the_shared_launch(n_chan, tuned):
+    """360 channels, 128 trials, one split chunk of 65536 samples: alone the grid kernel is the fastest,
+    in a tuned batch the direct kernel, whose beams share a launch.  With 1000 channels the grid is in
+    both.  Untuned batches run what the beams' own plans run."""
+    n = 1 << 16
+    freqs = 1250.0 + (np.arange(n_chan) + 0.5) * (300.0 / n_chan)
+    plans = [fdd.Plan(freqs, 1550.0, 64e-6, np.linspace(0.0, 400.0, 128), n, n, single_chunk=True, precision="fp16_split",
+                      workspace=False) for _ in range(2)]
+    assert all(p.grid[0] == 1 for p in plans)
+    xs = [torch.randn((n_chan, n), device="cuda") for _ in plans]
+    outs = {}
+    for autotune in (False, True):
+        with fdd.Batch(plans, autotune=autotune) as b:
+            outs[autotune] = [y.clone() for y in b.execute(xs)]
+            torch.cuda.synchronize()
+            grid = [c["choice"] == "grid" for c in b.describe()["classes"]]
+        assert grid == [tuned if autotune else True]
+    for y, e in zip(outs[True], outs[False]):
+        assert float((y - e).norm() / e.norm()) < 1e-5          # the split products keep within 1e-6
+    for p in plans:
+        p.close()
