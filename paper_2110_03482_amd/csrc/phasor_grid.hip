@@ -116,6 +116,12 @@ constexpr int grid_bins() {
 }
 constexpr int kTaps = 8;
 
+// Four powers of a row of the caller's output, which may begin at any float: the compiler is told
+// so, and gfx950 writes them in one access all the same.
+struct __attribute__((packed, aligned(4))) PowerQuad {
+  float a, b, c, d;
+};
+
 // phi on its unit pieces: tap i (grid point floor(x) - 3 + i) has the weight P_i(r), tap 7 - i the
 // weight P_i(-r), r = x - floor(x) - 1/2; ascending powers of r; integral of phi = 1.
 // Made by reweighted least squares: of all such phi the one whose worst ratio of aliases (frequencies
@@ -721,8 +727,8 @@ __global__ __launch_bounds__(64 * grid_bins<POWER>(), 1) void k_phasor_grid(Grid
             if (f0 + w == 0) y.x += a.dc_add;
             pw[w] = fmaf(y.x, y.x, y.y * y.y);
           }
-          float4* const to = reinterpret_cast<float4*>(a.P + (int64_t)dm * a.n_pow_bins + f0);
-          *(ok && f0 < a.n_pow_bins ? to : dump) = make_float4(pw[0], pw[1], pw[2], pw[3]);
+          PowerQuad* const to = reinterpret_cast<PowerQuad*>(a.P + (int64_t)dm * a.n_pow_bins + f0);
+          *(ok && f0 < a.n_pow_bins ? to : reinterpret_cast<PowerQuad*>(dump)) = {pw[0], pw[1], pw[2], pw[3]};
         } else {
           const float2 y0 = smem[(2 * ho) * S::RP + row], y1 = smem[(2 * ho + 1) * S::RP + row];
           float4* const to = reinterpret_cast<float4*>(a.Yc + (int64_t)dm * yrow + (int64_t)k * a.pitch + f0 + 2 * ho);

@@ -58,3 +58,19 @@ def test_power_of_a_down_sampling_plan(case, monkeypatch):
             assert torch.equal(P, p.power_spectrum(xd))
     ref = O.fdd_power(x, kind, w.dms, w.freqs, w.ref_freq_mhz, w.tsamp_s, w.chunk_len, mode="exact")
     check_power(P.cpu().numpy(), ref, TOL, skip_dc=kind == "u8", label=f"power of a down-sampling plan {case}")
+
+
+def test_power_into_an_output_at_any_float(monkeypatch):
+    monkeypatch.setenv("FDD_GRID", "1")
+    w, x = make(10, 70, 2048, 100, "f32", 20.0)
+    xd = torch.from_numpy(np.ascontiguousarray(x)).cuda()
+    with plan_of(w, power_only=True) as p:
+        assert p.grid[0] == 1
+        P = p.power_spectrum(xd)
+        for off in (1, 2, 3):
+            flat = torch.full((P.numel() + 8,), -1.0, device="cuda")
+            out = flat[off:off + P.numel()].view(P.shape)
+            assert p.power_spectrum(xd, out) is out
+            torch.cuda.synchronize()
+            assert torch.equal(out, P)
+            assert bool((flat[:off] == -1.0).all()) and bool((flat[off + P.numel():] == -1.0).all())
