@@ -100,7 +100,7 @@ struct GridArgs {
   const uint4* ctab = nullptr;      // [n_blk][n_chan] {turns per bin of one DM step (lo, hi), of the
                                     // block's centre trial blk / 2 (lo, hi)}
   const int* perm = nullptr;        // [n_chan] channel of each table entry (entries by ascending delay)
-  uint4* sched = nullptr;           // scratch: schedules of the launch's waves,
+  uint4* sched = nullptr;           // scratch: schedules of the launch's waves (null where values are staged),
   uint16_t* places = nullptr;       // [groups of bins][sched_len] orders of the channels,
   int* turns = nullptr;             // [groups of bins], and
   float4* dump = nullptr;           // 16 bytes per lane that nobody reads
@@ -330,13 +330,19 @@ hipError_t launch_phasor_facw(const PhasorArgs& a, int precision, int nt, hipStr
 // The non-uniform transform along the trial axis, and its row divisors.
 constexpr int kGridLogMin = 8, kGridLogMax = 12;   // grid points per column, 2^8 .. 2^12
 constexpr int kGridWaves = 1024;                    // waves of a launch at most (four per CU)
+constexpr int kGridStaged = 16;                     // spread steps at most whose values are staged
+inline int grid_steps(int n_chan, int log_m) {
+  const int lm = 1 << (log_m - 6);
+  return 2 * ((n_chan + 2 * lm - 1) / (2 * lm));
+}
 // Schedule entries per wave: every channel once, in equal parts per lane.
 inline int grid_sched_len(int n_chan) { return (n_chan + 127) / 128 * 128; }
 inline int64_t grid_groups(int64_t n_bins, int log_gb) { return (n_bins + (int64_t(1) << log_gb) - 1) >> log_gb; }
-// Scratch of a launch: the schedules (an entry per channel and wave), the dump, then per group of
-// bins the turns and the places.
-inline size_t grid_sched_bytes(int n_chan) {
-  return (size_t)kGridWaves * ((size_t)grid_sched_len(n_chan) * sizeof(uint4) + 64 * sizeof(float4));
+// Scratch of a launch: the schedules (an entry per channel and wave) unless the values are staged, the
+// dump, then per group of bins the turns and the places.
+inline size_t grid_sched_bytes(int n_chan, int log_m) {
+  const size_t entries = grid_steps(n_chan, log_m) > kGridStaged ? (size_t)grid_sched_len(n_chan) : 0;
+  return (size_t)kGridWaves * (entries * sizeof(uint4) + 64 * sizeof(float4));
 }
 inline size_t grid_order_bytes(int n_chan, int64_t n_bins, int log_gb) {
   return (size_t)grid_groups(n_bins, log_gb) * (sizeof(int) + (size_t)grid_sched_len(n_chan) * sizeof(uint16_t));
@@ -344,9 +350,10 @@ inline size_t grid_order_bytes(int n_chan, int64_t n_bins, int log_gb) {
 inline void grid_set_scratch(GridArgs* a, uint8_t* mem, int n_chan, int64_t n_bins) {
   a->n_groups = grid_groups(n_bins, a->log_gb);
   a->sched_len = grid_sched_len(n_chan);
-  a->sched = (uint4*)mem;
-  a->dump = (float4*)(a->sched + (size_t)kGridWaves * (size_t)a->sched_len);
-  a->turns = (int*)(mem + grid_sched_bytes(n_chan));
+  const size_t bytes = grid_sched_bytes(n_chan, a->log_m);
+  a->sched = grid_steps(n_chan, a->log_m) > kGridStaged ? (uint4*)mem : nullptr;
+  a->dump = (float4*)(mem + bytes) - (size_t)kGridWaves * 64;
+  a->turns = (int*)(mem + bytes);
   a->places = (uint16_t*)(a->turns + a->n_groups);
 }
 hipError_t launch_phasor_grid(const GridArgs& a, hipStream_t st);

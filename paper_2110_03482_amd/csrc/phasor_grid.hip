@@ -760,10 +760,9 @@ hipError_t launch_grid(const GridArgs& a, hipStream_t st) {
   hipLaunchKernelGGL((k_grid_order<LOGM>), dim3((unsigned)grid_groups(bins, a.log_gb)), dim3(64), 0, st, a);
   const hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  constexpr int LM = GridShape<LOGM>::LM;
-  const int steps = 2 * ((a.n_chan + 2 * LM - 1) / (2 * LM));
+  const int steps = grid_steps(a.n_chan, LOGM);
   if (steps <= 8) return launch_grid_ns<LOGM, 8, POWER>(a, st);
-  if (steps <= 16) return launch_grid_ns<LOGM, 16, POWER>(a, st);
+  if (steps <= kGridStaged) return launch_grid_ns<LOGM, kGridStaged, POWER>(a, st);
   return launch_grid_ns<LOGM, 0, POWER>(a, st);
 }
 
@@ -781,11 +780,12 @@ hipError_t launch_grid_m(const GridArgs& a, hipStream_t st) {
 }  // namespace
 
 hipError_t launch_phasor_grid(const GridArgs& a, hipStream_t st) {
-  if (a.X == nullptr || a.ctab == nullptr || a.dec == nullptr || a.perm == nullptr || a.sched == nullptr ||
-      a.places == nullptr || a.turns == nullptr || a.dump == nullptr || a.sched_len < grid_sched_len(a.n_chan) || a.window < 2 ||
-      (a.Yc == nullptr) == (a.P == nullptr) || a.n_dm < 1 || a.n_chan < 1 || a.n_chan > 65535 || a.n_chunks < 1 ||
-      a.blk < 1 || 2 * a.blk > (1 << a.log_m) || (int64_t)a.n_blk * a.blk < a.n_dm || (a.n_blk > 1 && a.log_m != 12) ||
-      (a.P != nullptr && (a.n_chunks != 1 || a.log_m != 12)) ||
+  if (a.log_m < kGridLogMin || a.log_m > kGridLogMax || a.X == nullptr || a.ctab == nullptr || a.dec == nullptr ||
+      a.perm == nullptr || a.places == nullptr || a.turns == nullptr || a.dump == nullptr ||
+      (a.sched == nullptr && grid_steps(a.n_chan, a.log_m) > kGridStaged) || a.sched_len < grid_sched_len(a.n_chan) ||
+      a.window < 2 || (a.Yc == nullptr) == (a.P == nullptr) || a.n_dm < 1 || a.n_chan < 1 || a.n_chan > 65535 ||
+      a.n_chunks < 1 || a.blk < 1 || 2 * a.blk > (1 << a.log_m) || (int64_t)a.n_blk * a.blk < a.n_dm ||
+      (a.n_blk > 1 && a.log_m != 12) || (a.P != nullptr && (a.n_chunks != 1 || a.log_m != 12)) ||
       grid_groups(a.P != nullptr ? a.n_pow_bins : a.n_bins, a.log_gb) > a.n_groups)
     return hipErrorInvalidValue;
   return launch_grid_m(a, st);

@@ -221,7 +221,7 @@ static double grid_us(const fdd_plan_s* p, int N, const std::vector<GridRun>& ru
     const double its = (double)((N + per - 1) / per) * r.n_blk;
     const double rounds = std::ceil(pairs * its / kBlocks);
     const double setups = std::max(1.0, std::ceil(pairs * r.n_blk / kBlocks));
-    const int steps = 2 * ((n_chan + 2 * lm - 1) / (2 * lm));
+    const int steps = grid_steps(n_chan, r.log_m);
     const double round = steps <= 8 ? kRoundUs[0] : steps <= 16 ? kRoundUs[1] : kBaseUs + kStepUs * steps;
     us += kStartUs + rounds * (apart ? kApart * round : round) + setups * kBatchUs * (double)((n_chan + 63) / 64);
   }
@@ -294,7 +294,7 @@ int64_t grid_scratch_bins(const fdd_plan_s* p, const GridRun& r) {
 
 // Scratch of one run's launches.
 size_t grid_scratch_bytes(const fdd_plan_s* p, const GridRun& r) {
-  return grid_sched_bytes(p->desc.n_chan) + grid_order_bytes(p->desc.n_chan, grid_scratch_bins(p, r), r.log_gb);
+  return grid_sched_bytes(p->desc.n_chan, r.log_m) + grid_order_bytes(p->desc.n_chan, grid_scratch_bins(p, r), r.log_gb);
 }
 
 // The plan's trials as runs of equal steps (as uniform_grid tests them), each inside one segment;

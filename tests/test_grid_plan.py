@@ -25,6 +25,20 @@ def test_scratch_of_a_down_sampled_single_chunk_plan_holds_all_bins(L, dm_max, f
         assert p.geometry.workspace_bytes >= full + 8 * (L // factor)
 
 
+@pytest.mark.parametrize("n_chan,n_dm", [(200, 400), (256, 1000), (512, 2048)])
+def test_no_schedules_where_values_are_staged(n_chan, n_dm, monkeypatch):
+    """Up to 16 spread steps per column group the grid kernel writes no schedule: beyond the plan of the
+    family it needs 1 MiB for rows that are no trials, its channel tables and row divisors (under 64
+    KiB), and a few groups of bins (small DM steps: 1024 bins a group)."""
+    got = {}
+    for form in ("0", "1"):
+        monkeypatch.setenv("FDD_GRID", form)
+        with dry(n_chan, 100000, np.linspace(0.0, 2.0, n_dm), 8192) as p:
+            assert p.grid[0] == int(form)
+            got[form] = p.geometry.workspace_bytes
+    assert got["1"] <= got["0"] + (1 << 20) + (1 << 16)
+
+
 # Measured phasor stages of both forms on an MI355X, us (family, grid): chunks, L, channels, trials, precision.
 # A single chunk is a circular transform, two are 1.25 L samples.
 MEASURED = [
