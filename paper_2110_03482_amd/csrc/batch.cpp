@@ -853,8 +853,7 @@ fdd_status fdd_batch_create(int32_t n, const fdd_plan_t* plans, const fdd_batch_
         for (const GridRun& r : sk.grid) {
           grid_table(sk.rep, r, &tab);
           std::memcpy(tabs.data() + r.ctab, tab.data(), tab.size() * sizeof(uint4));
-          std::vector<float> dv;
-          grid_divisors(r.log_m, &dv);
+          const std::vector<float>& dv = grid_divisors(r.log_m);
           std::memcpy(tabs.data() + r.dec, dv.data(), dv.size() * sizeof(float));
         }
         continue;

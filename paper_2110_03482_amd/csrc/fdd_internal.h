@@ -357,7 +357,7 @@ inline void grid_set_scratch(GridArgs* a, uint8_t* mem, int n_chan, int64_t n_bi
   a->places = (uint16_t*)(a->turns + a->n_groups);
 }
 hipError_t launch_phasor_grid(const GridArgs& a, hipStream_t st);
-void grid_divisors(int log_m, std::vector<float>* out);
+const std::vector<float>& grid_divisors(int log_m);   // kGridLogMin .. kGridLogMax
 // Spin-frequency-scaled DMs: the per-block matrix products and the resampling in DM.
 // precision FDD_FP32: plain X; split precisions: X split in place by launch_split_x, and the
 // per-chunk L1 maxima for the scale.

@@ -42,6 +42,7 @@
 // float32: 13.6 to 14.4 ms (matrix product 104 ms; reading X and writing Y once takes 3.6 ms); 512
 // channels, 2048 trials, one chunk of 2^22 samples, powers: 36.7 ms (113 ms).
 #include <cmath>
+#include <mutex>
 
 #include "device_math.h"
 #include "fdd_internal.h"
@@ -794,14 +795,14 @@ hipError_t launch_phasor_grid(const GridArgs& a, hipStream_t st) {
 // Row divisors 1 / phihat((idx - M/4) / M), idx < M/2, phihat the Fourier transform of the
 // piecewise polynomial phi (8-point Gauss-Legendre per piece: exact for degree 7 times the
 // cosine's expansion to well below float64 rounding of the result at |k| <= M/4).
-void grid_divisors(int log_m, std::vector<float>* out) {
+static std::vector<float> make_divisors(int log_m) {
   static const double kX[8] = {0.0950125098376374, 0.2816035507792589, 0.4580167776572274, 0.6178762444026438,
                                0.7554044083550030, 0.8656312023878318, 0.9445750230732326, 0.9894009349916499};
   static const double kW[8] = {0.1894506104550685, 0.1826034150449236, 0.1691565193950025, 0.1495959888165767,
                                0.1246289712555339, 0.0951585116824928, 0.0622535239386479, 0.0271524594117541};
   const TapTable t{};
   const int half = 1 << (log_m - 1);
-  out->resize((size_t)half);
+  std::vector<float> out((size_t)half);
   for (int idx = half / 2; idx <= half; ++idx) {      // even in idx - half / 2
     const double om = 2.0 * 3.14159265358979323846 * (double)(idx - half / 2) / (double)(2 * half);
     double sum = 0.0;
@@ -812,9 +813,19 @@ void grid_divisors(int log_m, std::vector<float>* out) {
         for (int d = 7; d >= 0; --d) p = p * r + (double)t.c[i][d];
         sum += 2.0 * wt * p * std::cos(om * ((double)i - 3.5 - r));   // taps i and 7 - i
       }
-    if (idx < half) (*out)[(size_t)idx] = (float)(1.0 / sum);
-    (*out)[(size_t)(half - idx)] = (float)(1.0 / sum);
+    if (idx < half) out[(size_t)idx] = (float)(1.0 / sum);
+    out[(size_t)(half - idx)] = (float)(1.0 / sum);
   }
+  return out;
+}
+
+// They depend on the grid alone and take 64 cosines each (half of them): made once per process and size.
+const std::vector<float>& grid_divisors(int log_m) {
+  static std::once_flag made[kGridLogMax - kGridLogMin + 1];
+  static std::vector<float> tab[kGridLogMax - kGridLogMin + 1];
+  const int i = log_m - kGridLogMin;
+  std::call_once(made[i], [&] { tab[i] = make_divisors(log_m); });
+  return tab[i];
 }
 
 }  // namespace fdd

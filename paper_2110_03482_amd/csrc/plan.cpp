@@ -449,8 +449,7 @@ static void build_host_tables(fdd_plan_s* p) {
     std::vector<uint4> ct;
     grid_table(p, r, &ct);
     keep(r.ctab, ct.data(), ct.size() * sizeof(uint4));
-    std::vector<float> dv;
-    grid_divisors(r.log_m, &dv);
+    const std::vector<float>& dv = grid_divisors(r.log_m);
     keep(r.dec, dv.data(), dv.size() * sizeof(float));
   }
   if (p->lin) {

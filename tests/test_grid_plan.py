@@ -1,4 +1,6 @@
 """Planning of the grid form of the phasor sum, on dry-run plans (no GPU)."""
+import time
+
 import numpy as np
 import pytest
 
@@ -37,6 +39,21 @@ def test_no_schedules_where_values_are_staged(n_chan, n_dm, monkeypatch):
             assert p.grid[0] == int(form)
             got[form] = p.geometry.workspace_bytes
     assert got["1"] <= got["0"] + (1 << 20) + (1 << 16)
+
+
+def test_planning_takes_no_longer_than_the_family(monkeypatch):
+    """The row divisors depend on the grid alone and are made once.  Per plan the grid form then does
+    less than the factorised one (no phase table): 1.29 against 1.57 ms of this thread's time."""
+    best = {"0": 1.0, "1": 1.0}
+    dms = np.linspace(0.0, 20.0, 2048)
+    for _ in range(40):
+        for form in best:
+            monkeypatch.setenv("FDD_GRID", form)
+            t0 = time.thread_time()
+            with dry(64, 4096, dms, 4096, single_chunk=True) as p:
+                best[form] = min(best[form], time.thread_time() - t0)
+                assert p.grid[0] == int(form)
+    assert best["1"] <= best["0"]
 
 
 # Measured phasor stages of both forms on an MI355X, us (family, grid): chunks, L, channels, trials, precision.
