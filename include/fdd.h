@@ -291,7 +291,9 @@ fdd_status fdd_smearing_factors(int32_t n_chan, const double* chan_freq_mhz, dou
                                 const double* dm, int32_t max_factor, int32_t* out);
 /* The plan's float64 delay table tau[n_dm][n_chan] of Eq. 1 (host copy). */
 fdd_status fdd_plan_delays(fdd_plan_t plan, double* tau_out);
-/* Infrastructure: name of the phasor-sum kernel family a plan selected ("valu", "mfma_f32", ...). */
+/* Infrastructure: name of the phasor-sum kernel family a plan selected ("valu", "mfma_f32", ...).  Where
+ * fdd_plan_grid reports runs, the grid form does the sums of fdd_execute and fdd_power_spectrum, and
+ * the family is the one that does them without it (FDD_GRID=0). */
 const char* fdd_plan_kernel(fdd_plan_t plan);
 /* Infrastructure: the DM factorisation a plan uses for a uniform grid with exact delays (Eq. 1 is
  * linear in DM, so trial a*fine + b has the delay of coarse trial a plus that of fine offset b

@@ -268,6 +268,7 @@ def fdd_smearing_factors(freqs_mhz, tsamp_s: float, dms, max_factor: int) -> np.
 
 
 def fdd_plan_kernel(plan) -> str:
+    """The plan's kernel family; it does the phasor sums only where fdd_plan_grid gives no runs."""
     return library().fdd_plan_kernel(plan).decode()
 
 
