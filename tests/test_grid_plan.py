@@ -41,6 +41,57 @@ def test_no_schedules_where_values_are_staged(n_chan, n_dm, monkeypatch):
     assert got["1"] <= got["0"] + (1 << 20) + (1 << 16)
 
 
+def test_plans_keep_fitting_the_static_scratch(monkeypatch):
+    """A plan that fits the 64 MiB of fdd_execute_noalloc without the grid's schedules fits them with
+    FDD_GRID=1, too: it gives up the grid form instead."""
+    limit = 64 << 20
+    kept = dropped = 0
+    for n_dm in range(100, 520, 20):
+        size, grid = {}, {}
+        for form in ("0", "1"):
+            monkeypatch.setenv("FDD_GRID", form)
+            with dry(420, 1 << 14, np.linspace(0.0, 30.0, n_dm), 4096) as p:
+                size[form], grid[form] = p.geometry.workspace_bytes, p.grid[0]
+        assert grid["0"] == 0
+        if size["0"] <= limit:
+            assert size["1"] <= limit
+            kept += grid["1"] == 1
+            dropped += grid["1"] == 0
+        else:
+            assert grid["1"] == 1
+    assert kept > 0 and dropped > 0
+
+
+STEPPED = np.cumsum(np.concatenate([[0.0], np.full(99, 0.5), np.full(100, 1.0), np.full(101, 2.0)]))
+
+
+@pytest.mark.parametrize("dms,kw,runs", [
+    (np.linspace(0.0, 50.0, 64), {}, 1), (np.linspace(0.0, 50.0, 63), {}, 0),             # the shortest run
+    (STEPPED, {}, 3), (STEPPED[:170], {}, 2), (STEPPED[:163], {}, 0),                     # a run of 63 trials
+    (STEPPED[::-1], {}, 0), (np.sqrt(np.arange(300.0)), {}, 0), (np.zeros(100), {}, 0),
+    (np.linspace(7.0, 50.0, 300), {}, 1),                                                 # does not begin at 0
+    (np.linspace(0.0, 50.0, 300), {"mode": "round"}, 0),
+    (np.linspace(0.0, 50.0, 300), {"downsample": [1] * 150 + [2] * 150}, 2),              # runs end with a segment
+    (np.linspace(0.0, 50.0, 300), {"downsample": [1] * 250 + [2] * 50}, 0),
+    (np.linspace(0.0, 50.0, 5000), {}, 1)])
+def test_runs_of_equal_steps(dms, kw, runs, monkeypatch):
+    monkeypatch.setenv("FDD_GRID", "1")
+    with dry(40, 40000, dms, 8192, **kw) as p:
+        assert p.grid[0] == runs
+        assert p.grid[1] == 0 if runs == 0 else 256 <= p.grid[1] <= 4096
+        assert runs == 0 or p.grid[1] == 4096 or p.grid[1] >= 2 * dms.size // runs - 4
+
+
+@pytest.mark.parametrize("env", ["FDD_FACTOR", "FDD_TILE_VARIANT", "FDD_PHASE_TABLE"])
+def test_a_family_asked_for_by_name_keeps_its_kernels(env, monkeypatch):
+    dms = np.linspace(0.0, 1000.0, 2048)
+    with dry(1024, 1 << 20, dms, 1 << 16) as p:
+        assert p.grid[0] == 1
+    monkeypatch.setenv(env, {"FDD_FACTOR": "direct", "FDD_TILE_VARIANT": "0", "FDD_PHASE_TABLE": "linear"}[env])
+    with dry(1024, 1 << 20, dms, 1 << 16) as p:
+        assert p.grid == (0, 0)
+
+
 def test_planning_takes_no_longer_than_the_family(monkeypatch):
     """The row divisors depend on the grid alone and are made once.  Per plan the grid form then does
     less than the factorised one (no phase table): 1.29 against 1.57 ms of this thread's time."""
