@@ -37,10 +37,12 @@
 //  - The transform goes in two in-register passes, 64 points over stride M / 64 and M / 64 points
 //    over the rest, with one exchange through LDS between them; of the second pass only the quarter
 //    of the outputs at each end is wanted, and the workgroup writes them row by row through LDS.
-// Bound: instruction issue and LDS latency of one wave per SIMD (VALU 37 % and LDS 39 % of the
-// cycles; the waits are what is left).  At 1024 channels, 2048 trials, 21 chunks of 65536 samples,
-// float32: 13.6 to 14.4 ms (matrix product 104 ms; reading X and writing Y once takes 3.6 ms); 512
-// channels, 2048 trials, one chunk of 2^22 samples, powers: 36.7 ms (113 ms).
+// Bound: instruction issue and LDS of one wave per SIMD.  At 1024 channels, 2048 trials, 21 chunks of
+// 65536 samples, float32: 13.2 to 14.0 ms (matrix product 104 ms; reading X and writing Y once takes
+// 3.6 ms); VALU issue 40 % of the cycles, LDS busy in 48 % (half of that bank conflicts), waits for
+// memory or LDS 19 %.  512 channels, 2048 trials, one chunk of 2^22 samples, powers: 38 ms (113 ms),
+// 18 ns per transform (the other: 20); VALU 37 %, LDS 33 %, waits 24 %: a bin's entries serve
+// one column only, and 35 GB are written for 17.
 #include <cmath>
 #include <mutex>
 

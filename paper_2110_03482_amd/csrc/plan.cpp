@@ -199,7 +199,8 @@ void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out) 
 // and runs on 512 workgroups at a time, more steps cost kStepUs each on top of a base without staged
 // values, and the entries of a bin kBatchUs per 64 channels.  90 % of the shapes lie within -12 and
 // +10 % of it.  Rows of Y that lie a multiple of 16 KiB apart, N a multiple of 32, share few memory
-// channels where they exceed the last cache: 64 chunks of 16384, 589 trials 7.1 ms against 3.0.
+// channels where they exceed the last cache, kApart: 64 chunks of 16384, 589 trials took 7.1 ms where
+// the terms above give 3.0; seven such shapes lay between 1.0 and 2.4 times their estimate.
 // The families, per segment: a start, the matrix products of whole tiles (64 trials in the direct
 // kernels and 64 coarse rows of phasor_fac_fine(N) trials in the factorised ones, by whole tiles of 8
 // chunks in the direct ones), the phasors, and the sums written.  90 % lie within -25 and +15 %.
