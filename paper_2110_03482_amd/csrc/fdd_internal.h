@@ -270,6 +270,8 @@ hipError_t launch_r2c_long(const FftArgs& a, float2* work, float* l1sum, hipStre
 hipError_t launch_c2r_long(const FftArgs& a, float2* work, float2* work2, hipStream_t st);
 constexpr int kMaxBlockLogN = 15;   // longest transform held by one workgroup: 2^15 complex points
 hipError_t launch_phasor_valu(const PhasorArgs& a, hipStream_t st);
+int phasor_valu_chunks(int n_chunks);                             // chunks and bins of a lane in that launch
+int phasor_valu_bins(int n_bins, int n_dm, int n_chunks);
 hipError_t launch_phasor_mfma_f32(const PhasorArgs& a, hipStream_t st);
 // The single-plan split kernels read X as split words: call launch_split_x on X first (in
 // place; X then no longer holds spectra).  The grouped split kernels read plain X.

@@ -193,16 +193,24 @@ hipError_t launch_valu(const PhasorArgs& a, hipStream_t st) {
   return hipGetLastError();
 }
 
-// The most bins per lane that leave 512 workgroups, two per CU.
 template <int NK>
 hipError_t launch_valu_nk(const PhasorArgs& a, hipStream_t st) {
-  const int64_t rows = (int64_t)((a.n_dm + kDms - 1) / kDms) * ((a.n_chunks + NK - 1) / NK);
-  const auto blocks = [&](int fv) { return rows * ((a.n_bins + 64 * fv - 1) / (64 * fv)); };
-  if (blocks(kAcc / NK) >= 512) return launch_valu<kAcc / NK, NK>(a, st);
-  if (NK == 1 && blocks(4) >= 512) return launch_valu<4, NK>(a, st);
+  const int fv = phasor_valu_bins(a.n_bins, a.n_dm, a.n_chunks);
+  if (fv == kAcc / NK) return launch_valu<kAcc / NK, NK>(a, st);
+  if (NK == 1 && fv == 4) return launch_valu<4, NK>(a, st);
   return launch_valu<1, NK>(a, st);
 }
 }  // namespace
+
+int phasor_valu_chunks(int n_chunks) { return n_chunks <= 2 ? n_chunks : 4; }
+
+// The most bins per lane that leave 512 workgroups, two per CU.
+int phasor_valu_bins(int n_bins, int n_dm, int n_chunks) {
+  const int nk = phasor_valu_chunks(n_chunks);
+  const int64_t rows = (int64_t)((n_dm + kDms - 1) / kDms) * ((n_chunks + nk - 1) / nk);
+  const auto blocks = [&](int fv) { return rows * ((n_bins + 64 * fv - 1) / (64 * fv)); };
+  return blocks(kAcc / nk) >= 512 ? kAcc / nk : nk == 1 && blocks(4) >= 512 ? 4 : 1;
+}
 
 int64_t phasor_valu_tiles(PhasorArgs* a, int nk) {
   const int bins = 64 * kAcc / nk;

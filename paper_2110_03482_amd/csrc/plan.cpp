@@ -193,86 +193,98 @@ void grid_table(const fdd_plan_s* p, const GridRun& r, std::vector<uint4>* out) 
 }
 
 // Whether the grid kernel is expected to be faster than the plan's family: a model of both, fitted to
-// the phasor stage of 786 shapes in both forms (4096 to 2^20 samples a chunk, 1 to 310 chunks, 16 to
-// 1024 channels, 64 to 4096 trials) and checked on 1037 others.
-// The grid kernel: a column group (its transform, stores and up to 8 or 16 spread steps) costs kRoundUs
-// and runs on 512 workgroups at a time, more steps cost kStepUs each on top of a base without staged
-// values, and the entries of a bin kBatchUs per 64 channels.  90 % of the shapes lie within -12 and
-// +10 % of it.  Rows of Y that lie a multiple of 16 KiB apart, N a multiple of 32, share few memory
+// the phasor stage of 1823 shapes in both forms (4096 to 2^20 samples a chunk, 1 to 310 chunks, 16 to
+// 1024 channels, 64 to 4096 trials).  E.g. two chunks of 65536 (grid, fac): split, 91 channels, 218
+// trials 407 and 267 us; 164 channels, 360 trials 459 and 453; 256 channels, 316 trials 470 and 651;
+// FP32, 52 channels, 388 trials 427 and 323; 105 channels, 139 trials 410 and 592.
+//
+// The grid kernel: a column group (its transform and stores) costs kRoundUs on grids of up to 1024 and of
+// more points and runs on 512 workgroups at a time; a spread step costs kStepUs with up to 8, up to 16
+// and more steps, and the entries of a bin kBatchUs per 64 channels.  90 % of the shapes lie within -12
+// and +12 % of it.  Rows of Y that lie a multiple of 16 KiB apart, N a multiple of 32, share few memory
 // channels where they exceed the last cache, kApart: 64 chunks of 16384, 589 trials took 7.1 ms where
 // the terms above give 3.0; seven such shapes lay between 1.0 and 2.4 times their estimate.
-// The families, per segment: a start, the matrix products of whole tiles (64 trials in the direct
-// kernels and 64 coarse rows of phasor_fac_fine(N) trials in the factorised ones, by whole tiles of 8
-// chunks in the direct ones), the phasors, and the sums written.  90 % lie within -25 and +15 %.
-// Near the line either form may be the faster one, so the grid has to win by kMargin: 841 of the 1823
-// shapes then take it, and 5 of those are slower than their family, by 7 % at most.
-// E.g. two chunks of 65536 (grid, fac): split, 91 channels, 218 trials 407 and 267 us; 164 channels, 360
-// trials 459 and 453; 256 channels, 316 trials 470 and 651; FP32, 52 channels, 388 trials 427 and 323;
-// 105 channels, 139 trials 410 and 592.
 static double grid_us(const fdd_plan_s* p, int N, const std::vector<GridRun>& runs) {
-  constexpr double kRoundUs[2] = {11.5, 13.9}, kBaseUs = 10.0, kStepUs = 0.405, kBatchUs = 0.47, kStartUs = 20.0;
-  constexpr double kBlocks = 512.0, kApart = 1.6;
+  constexpr double kStartUs = 19.5, kRoundUs[2] = {9.7, 11.0}, kStepUs[3] = {0.32, 0.24, 0.417}, kBatchUs = 0.36;
+  constexpr double kBlocks = 512.0, kApart = 1.3;
   const int n_chan = p->desc.n_chan;
   const bool apart = N % 32 == 0 && (double)p->desc.n_dm * (double)N * (double)p->pitch * 8.0 > 256e6;
   double us = 0.0;
   for (const GridRun& r : runs) {
     const double bins = (double)(p->L / p->segs[(size_t)r.seg].factor / 2 + 1);
-    const int lm = 1 << (r.log_m - 6), per = 64 / lm;
+    const int per = 1 << (kGridLogMax - r.log_m);
     const double pairs = std::ceil(bins / 2.0);
     const double its = (double)((N + per - 1) / per) * r.n_blk;
     const double rounds = std::ceil(pairs * its / kBlocks);
     const double setups = std::max(1.0, std::ceil(pairs * r.n_blk / kBlocks));
     const int steps = grid_steps(n_chan, r.log_m);
-    const double round = steps <= 8 ? kRoundUs[0] : steps <= 16 ? kRoundUs[1] : kBaseUs + kStepUs * steps;
+    const double round = kRoundUs[r.log_m > 10] + steps * kStepUs[steps <= 8 ? 0 : steps <= kGridStaged ? 1 : 2];
     us += kStartUs + rounds * (apart ? kApart * round : round) + setups * kBatchUs * (double)((n_chan + 63) / 64);
   }
   return us;
 }
 
+// The families, per segment: a start, whole rounds of one workgroup per CU (64 coarse rows of
+// phasor_fac_fine(N) trials and 4 bins in the factorised kernels; 64 trials, 8 bins and whole tiles of 8
+// chunks in the direct ones; 4 trials and 64 bins a lane in the vector kernel) of whole stages of
+// channels, and the sums written.  90 % of the shapes lie within -10 and +5 % (FP32) or -17 and +9 %
+// (split) of it in the factorised kernels, -22 and +16 % in the direct ones and -13 and +11 % in the
+// vector kernel.
 enum class Family { kVector, kFactorised, kChunked, kDirect };
-
-// Without the start of its launches (kStartUs of grid_pays).
-static double family_us(const fdd_plan_s* p, int N, Family fam, const Segment& sg) {
+struct FamilyUs {
+  double start, work;
+};
+static FamilyUs family_us(const fdd_plan_s* p, int N, Family fam, const Segment& sg) {
+  constexpr int kCus = 256;
   const auto up = [](int64_t n, int64_t to) { return (double)((n + to - 1) / to * to); };
+  const auto parts = [](int64_t n, int64_t of) { return (n + of - 1) / of; };
   const bool fp32 = p->desc.precision == FDD_FP32;
-  const int groups = chunk_groups(N);
-  const double bins = (double)(p->L / sg.factor / 2 + 1);
-  const double sums = 1e-6 * (double)sg.n * (double)N * bins;        // in millions, as what follows
-  const double rows = 1e-6 * bins * (double)p->desc.n_chan;
+  const int n_chan = p->desc.n_chan, groups = chunk_groups(N);
+  const int64_t bins = p->L / sg.factor / 2 + 1;
+  const double sums = 1e-6 * (double)sg.n * (double)N * (double)bins;
+  const double stages = 1e-3 * up(n_chan, fp32 ? 8 : 16);
   switch (fam) {
-    case Family::kVector: return up(sg.n, 4) * rows * (0.242 * N + 0.197);
-    case Family::kFactorised: {
-      const double tile = 64.0 * phasor_fac_fine(N);
-      const double work = 1e-6 * std::ceil(bins / 4.0) * std::ceil((double)sg.n / tile) * (double)p->desc.n_chan;
-      return fp32 ? 640.0 * work + 1.21 * sums : 310.0 * work + 2.09 * sums;
+    case Family::kVector: {
+      const int nk = phasor_valu_chunks(N), fv = phasor_valu_bins((int)bins, sg.n, N);
+      const double wg = up(parts(sg.n, 4) * parts(N, nk) * parts(bins, 64 * fv), kCus);
+      return {7.3, 1e-3 * wg * (double)parts(n_chan, 4) * (0.884 + fv * (0.182 * nk + 0.112)) + 2.8 * sums};
     }
-    case Family::kChunked: return up(sg.n, 64) * rows * (0.0341 * N + 0.0207 * groups) + 2.78 * sums;
+    case Family::kFactorised: {
+      const double wg = up(parts(bins, 4) * parts(parts(sg.n, phasor_fac_fine(N)), 64), kCus);
+      return fp32 ? FamilyUs{9.6, wg * 0.596 * stages + 1.45 * sums} : FamilyUs{8.8, wg * (0.286 * stages + 4.9e-4) + 2.05 * sums};
+    }
+    case Family::kChunked:
+      return {16.0, 1e-6 * up(sg.n, 64) * (double)bins * n_chan * (0.0341 * N + 0.0207 * groups) + 2.78 * sums};
     default: break;
   }
   double cols = 0.0;
   for (int g = 0; g < groups; ++g) cols += up(N / groups + (g < N % groups ? 1 : 0), 8);
-  if (fp32) return up(sg.n, 64) * rows * 0.0698 * cols + 2.86 * sums;
-  const double us = up(sg.n, 64) * rows * (0.0418 * cols + 0.030 * groups) + 2.47 * sums;
-  return p->desc.precision == FDD_FP16_SPLIT ? 0.94 * us : us;
+  const double wg = up(parts(sg.n, 64) * parts(bins, 8), kCus);
+  if (fp32) return {6.7 * groups, wg * stages * (0.033 * cols + 0.0077 * groups) + 2.53 * sums};
+  if (p->desc.precision == FDD_FP16_SPLIT) return {9.5 * groups, wg * stages * (0.019 * cols + 0.0135 * groups) + 2.63 * sums};
+  return {9.0 * groups, wg * stages * (0.0194 * cols + 0.0235 * groups) + 2.86 * sums};
 }
 
+// Near the line either form may be the faster one, so the grid has to win by kMargin: 896 of the shapes
+// then take it, of which 6 are slower than their family, by 9 % at most (19 of 942 without it).
 // `tuned`: against the best of the kernels that an autotuned batch chooses from, whose beams share a
 // launch, so that its start is no beam's own.
 static bool grid_pays(const fdd_plan_s* p, int N, const std::vector<GridRun>& runs, bool tuned) {
-  constexpr double kMargin = 1.1;
-  constexpr double kStartUs[4] = {20.0, 18.0, 16.0, 13.0};           // by family
-  const bool fp32 = p->desc.precision == FDD_FP32;
+  constexpr double kMargin = 1.05;
   const bool fac = p->fac_fine > 0 && p->facw_nt == 0 && N <= 2;
   const bool vec = fac ? p->fac_few && fac_few_pays(p, N) : p->kernel == "valu" && (N <= 2 || p->n_chunks > 2);
   const Family own = vec ? Family::kVector : fac ? Family::kFactorised : p->facw_nt > 0 ? Family::kChunked : Family::kDirect;
   double direct = 0.0;
   if (!tuned) {
-    for (const Segment& sg : p->segs) direct += kStartUs[(int)own] + family_us(p, N, own, sg);
+    for (const Segment& sg : p->segs) {
+      const FamilyUs us = family_us(p, N, own, sg);
+      direct += us.start + us.work;
+    }
   } else {
     const Segment& sg = p->segs[0];
-    direct = family_us(p, N, own == Family::kChunked ? Family::kDirect : own, sg);
-    if (runs.size() == 1 && phasor_fac_fine(N) > 0) direct = std::min(direct, family_us(p, N, Family::kFactorised, sg));
-    if (!fp32) direct = std::min(direct, family_us(p, N, Family::kDirect, sg));
+    direct = family_us(p, N, own == Family::kChunked ? Family::kDirect : own, sg).work;
+    if (runs.size() == 1 && phasor_fac_fine(N) > 0) direct = std::min(direct, family_us(p, N, Family::kFactorised, sg).work);
+    if (p->desc.precision != FDD_FP32) direct = std::min(direct, family_us(p, N, Family::kDirect, sg).work);
   }
   return kMargin * grid_us(p, N, runs) < direct;
 }
