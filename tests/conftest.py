@@ -27,3 +27,13 @@ def pytest_collection_modifyitems(config, items):
     for item in items:
         if "gpu" in item.keywords:
             item.add_marker(skip)
+
+
+@pytest.fixture(scope="session", autouse=True)
+def _oracle_in_threads():
+    from oracle import fdd_oracle
+
+    import oracle_threads
+    undo = oracle_threads.install(fdd_oracle)
+    yield
+    undo()
